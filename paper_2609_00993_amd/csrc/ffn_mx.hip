@@ -18,12 +18,11 @@
 //
 // Two tile shapes, as in the bf16 layer: the weight-streaming tile for small
 // batches (32 rows x 32 columns, one wave per workgroup, operands through
-// the wave's LDS stage) and, for large batches, 256 x 128 (gate + up) /
-// 256 x 256 tiles staged through a two-slot LDS ring of 128-deep K slices
-// (128 bytes per row, the byte layout of the bf16 ring's 64-deep slices),
-// with the slices' scale bytes staged alongside.  256-row tiles read an
-// expert of up to 256 rows' weights once; against 128-row tiles in a
-// three-slot ring they took the 8192-token layer's GEMM1 from 445 to 392 us.
+// the wave's LDS stage) and, for large batches, tiles of up to 256 rows by
+// 128 (gate + up) / 256 columns, cut to the 32-row blocks that they hold and
+// staged through LDS rings of 128-deep K slices (128 bytes per row, the byte
+// layout of the bf16 ring's 64-deep slices), with the scale bytes staged
+// alongside.
 #include <type_traits>
 
 #include "common.h"
@@ -322,15 +321,51 @@ __device__ __forceinline__ void gemm_mx_skinny_tile(const GemmArgsMX& g, const T
 
 // One workgroup of 4 waves, a BM x BN output tile of one expert.  Per
 // 128-deep K slice, A (BM rows) and B (BR = NB x BN weight rows) travel HBM ->
-// LDS by 16-byte DMA into a ring of STAGES slots (swizzled like the bf16
-// ring), and each row's four scale bytes of the slice (one per 32 values) by
-// 4-byte DMA into the slot's scale area.  Every wave issues the same number
-// of DMA instructions per slice (padding with a repeat of an A-scale gather
-// into a spare area), so vmcnt counts retire exactly whole slices.  A slice
+// LDS by 16-byte DMA (swizzled like the bf16 ring) into a ring of SA slots
+// for A and one of SB >= SA slots for B: the weights, whose first touch goes
+// to HBM, run one slice further ahead where the LDS has room for it.  A slice
 // is two 64-deep MFMA steps; fragments of the next step are read from LDS
-// while the current step's MFMAs run.
-template <int BM, int BR, int WM, int WN, bool GATED, int STAGES>
-__device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
+// while the current step's MFMAs run, and the slice's barrier sits between
+// its steps, when every wave holds step 1's fragments.  After the barrier of
+// slice kt its slots are free: A(kt + SA) goes out beside the MFMAs of step 1
+// and B(kt + SB) beside those of the next slice's step 0, so the queue holds
+// ..., A(kt + SA), B(kt + SB), A(kt + 1 + SA), ... in this order.
+//
+// Scale bytes (one per 32 values, four per row and slice) are gathered by
+// DMA from one line per row.  SC4 (K a multiple of 512, the scale arrays
+// 16-byte aligned): one 16-byte gather brings a row's scales of four slices
+// into a single buffer, read into registers at the group's first slice and
+// refilled after that slice's barrier; otherwise each slice gathers four bytes
+// per row into a slot that goes with A's.  A gather touches 64 lines whatever
+// its width, as many as the codes of 64 rows: with a gather per slice the
+// scales cost 12 % of the 8192-token layer's GEMM1 (368 us with every lane
+// reading one row's scales, 420 in full).
+//
+// Each wave counts its own DMA instructions: loads complete in order, every
+// wave issues the same ones (a gather is repeated where rows run out), so a
+// counted wait at a slice's barrier retires exactly what the next slice needs
+// (with a group's gathers in flight, two instructions more).
+constexpr int mx_scale_rows(int bm) { return (bm + 63) / 64 * 64; }  // A rows in whole gathers
+constexpr int kMxB = 256;                                             // weight rows of a ring tile
+constexpr int kMxMaxRows = 256;                                       // rows of the tallest ring tile
+// 16-byte chunks of LDS: the rings, and the scale area in its larger form.
+constexpr int mx_ring_chunks(int bm, int sa, int sb) {
+  return sa * bm * 8 + sb * kMxB * 8 + (sa > 4 ? sa : 4) * (mx_scale_rows(bm) + kMxB) / 4;
+}
+
+// Wait until at most NA min(CA, n) + NB min(CB, n) DMA instructions (and no LDS
+// operation) of this wave are in flight; n is wave-uniform, n >= 0.
+template <int NA, int NB, int CA, int CB, int N = (CA > CB ? CA : CB)>
+__device__ __forceinline__ void wait_rings_lgkm0(int n) {
+  if constexpr (N > 0) {
+    if (n < N) return wait_rings_lgkm0<NA, NB, CA, CB, N - 1>(n);
+  }
+  wait_vmcnt_lgkm0<NA*(CA < N ? CA : N) + NB * (CB < N ? CB : N)>();
+}
+
+template <int BM, int WM, int WN, int SA, int SB, bool GATED, bool SC4>
+__device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const TileCoord& tc, u32x4* lds) {
+  constexpr int BR = kMxB;
   constexpr int NB = GATED ? 2 : 1;
   constexpr int BN = BR / NB;
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -339,20 +374,21 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
   constexpr int CPR = 8;                            // 16-byte chunks per staged row
   constexpr int RPI = 8;                            // rows per 16-byte DMA instruction
   constexpr int A_INS = BM / RPI / 4, B_INS = BR / RPI / 4;
-  constexpr int SC_ALL = (BM + BR) / 64;            // 4-byte gathers of scale rows per slice
-  constexpr int SC_INS = (SC_ALL + 3) / 4;          // per wave, padded
-  constexpr int NPS = A_INS + B_INS + SC_INS;       // vector-memory ops per wave per slice
+  constexpr int SC_A = mx_scale_rows(BM), SC_W = SC_A + BR;  // scale rows of a slot
+  constexpr int SC_INS = 2;                         // gathers per wave: one of A's rows, one of B's
+  constexpr int NA = A_INS + (SC4 ? 0 : SC_INS);    // DMA instructions per wave of an A and a B group
   constexpr int A_CH = BM * CPR, B_CH = BR * CPR;
-  constexpr int SC_W = BM + BR + 64;                // scale words per slot (+ spare for padding)
   constexpr int NRD = 2 * (FM + FB), NMF = FM * FB;
   static_assert(WM * WN == 4, "four waves");
   static_assert(A_INS * RPI * 4 == BM && B_INS * RPI * 4 == BR, "slices split into whole DMA instructions");
-  static_assert(BM % 64 == 0 && BR % 64 == 0, "scale gathers of 64 rows");
+  static_assert(BR == 4 * 64 && SC_A <= 4 * 64, "one gather of 64 rows per wave");
   static_assert(FM * 32 == WTM && FN * 32 == WTN, "wave tile must be a multiple of 32x32");
-  static_assert(STAGES >= 2 && NPS * (STAGES - 1) < 64, "pipeline depth");
-  // each slot: A chunks, B chunks, then SC_W scale words (one array, so the
-  // compiler sees the DMA'd scale words and the ring as one object)
-  __shared__ u32x4 ring[STAGES][A_CH + B_CH + SC_W / 4];
+  static_assert(SA >= 2 && (SB == SA || SB == SA + 1) && NA * (SA - 1) + B_INS * (SB - 1) < 64, "pipeline depth");
+  constexpr bool BNOW = SB == 2;                    // B goes out with A
+  static_assert(SA <= 4, "a group's gathers, issued at its first slice, are older than the next group's A");
+  u32x4(*const ring_a)[A_CH] = reinterpret_cast<u32x4(*)[A_CH]>(lds);
+  u32x4(*const ring_b)[B_CH] = reinterpret_cast<u32x4(*)[B_CH]>(lds + SA * A_CH);
+  u32x4* const scales = lds + SA * A_CH + SB * B_CH;
 
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5;
@@ -362,65 +398,70 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
   const int KS = g.K / 32;  // scale bytes per row
   const int lrow = lane / CPR, lphys = lane % CPR;
 
-  __amdgpu_buffer_rsrc_t a_rsrc;
-  uint32_t a_off[A_INS];
-  const uint8_t* b_src[B_INS];
-  const uint8_t* sc_src[SC_INS];  // this lane's scale word of slice 0 (rows clamped into range)
-  int sc_dst[SC_INS];             // its 64-word group in the slot's scale area
-  auto set_sources = [&](const TileCoord& tc) {
-    const int m0 = __builtin_amdgcn_readfirstlane(tc.m0);
-    const int rows = min(__builtin_amdgcn_readfirstlane(tc.m_end) - m0, BM);
-    a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(g.A + (size_t)m0 * g.K), (short)0, rows * g.K,
-                                               kBufferRsrcWord3);
-    const int e = __builtin_amdgcn_readfirstlane(tc.e);
-    const uint8_t* Be = g.B + (size_t)e * g.b_stride;
-    const uint8_t* Bse = g.Bs + (size_t)e * g.bs_stride;
+  // All operands are read through buffer resources with 32-bit lane offsets:
+  // per-lane row and chunk in a vector register, the K offset (and B's row
+  // group) in the scalar one, so an issue takes no vector instruction.
+  // A's resource covers exactly the tile's rows of its expert: rows past the
+  // end lie outside it, so their loads return zeros and make no memory
+  // request.  Groups of eight weight rows past N (a multiple of 128) and scale
+  // rows past the end read the last ones; their outputs are never stored.
+  const int m0 = __builtin_amdgcn_readfirstlane(tc.m0);
+  const int m_end = __builtin_amdgcn_readfirstlane(tc.m_end);
+  const int n0 = __builtin_amdgcn_readfirstlane(tc.n0);
+  const int e = __builtin_amdgcn_readfirstlane(tc.e);
+  auto rsrc = [](const uint8_t* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, bytes, kBufferRsrcWord3);
+  };
+  const __amdgpu_buffer_rsrc_t a_rsrc = rsrc(g.A + (size_t)m0 * g.K, min(m_end - m0, BM) * g.K);
+  const __amdgpu_buffer_rsrc_t b_rsrc = rsrc(g.B + (size_t)e * g.b_stride, (int)g.b_stride);
+  const __amdgpu_buffer_rsrc_t as_rsrc = rsrc(g.As + (size_t)m0 * KS, (m_end - m0) * KS);
+  const __amdgpu_buffer_rsrc_t bs_rsrc = rsrc(g.Bs + (size_t)e * g.bs_stride, (int)g.bs_stride);
+  auto brow_of = [&](int r) {  // weight row of staged row r (a multiple of 8, or any row of such a group)
+    if (GATED) return r < BN ? n0 + r : g.up_row + n0 + r - BN;
+    return n0 + r < g.N ? n0 + r : g.N - 8 + (r & 7);
+  };
+  // Staged row r = 8 (wave INS + i) + lrow holds chunk c of its row at slot
+  // c ^ swz(r), and swz(r) depends on r modulo 16 alone.
+  int a_off[A_INS], b_off[2], b_row[B_INS];
 #pragma unroll
-    for (int i = 0; i < A_INS; ++i) {
-      const int r = (wave * A_INS + i) * RPI + lrow;
-      a_off[i] = (uint32_t)(r * g.K + (lphys ^ swz<64>(r)) * 16);
-    }
-    auto brow_of = [&](int r) {
-      if (GATED) return r < BN ? min(tc.n0 + r, g.N - 1) : g.up_row + min(tc.n0 + r - BN, g.N - 1);
-      return min(tc.n0 + r, g.N - 1);
-    };
+  for (int i = 0; i < A_INS; ++i) {
+    const int r = (wave * A_INS + i) * RPI + lrow;
+    a_off[i] = r * g.K + (lphys ^ swz<64>(r)) * 16;
+  }
 #pragma unroll
-    for (int i = 0; i < B_INS; ++i) {
-      const int r = (wave * B_INS + i) * RPI + lrow;
-      b_src[i] = Be + (size_t)brow_of(r) * g.K + (lphys ^ swz<64>(r)) * 16;
-    }
-    // Every gather is the same instruction (no branch in the K loop): A-scale
-    // rows past the expert's end are clamped to its last row (their outputs
-    // are never stored); padding gathers repeat rows 0..63 into the spare area.
+  for (int i = 0; i < 2; ++i) b_off[i] = lrow * g.K + (lphys ^ swz<64>((wave * B_INS + i) * RPI + lrow)) * 16;
 #pragma unroll
-    for (int i = 0; i < SC_INS; ++i) {
-      const int q = wave * SC_INS + i;
-      const int qq = q < SC_ALL ? q : 0;
-      const int r = qq * 64 + lane;
-      if (r < BM) sc_src[i] = g.As + (size_t)min(m0 + r, tc.m_end - 1) * KS;
-      else sc_src[i] = Bse + (size_t)brow_of(r - BM) * KS;
-      sc_dst[i] = __builtin_amdgcn_readfirstlane(q < SC_ALL ? q * 64 : BM + BR);
+  for (int i = 0; i < B_INS; ++i) b_row[i] = __builtin_amdgcn_readfirstlane(brow_of((wave * B_INS + i) * RPI)) * g.K;
+  const int sc_a = wave % (SC_A / 64) * 64;  // first A row of this wave's gather
+  const int sa_off = min(sc_a + lane, m_end - m0 - 1) * KS;
+  const int sb_off = brow_of(wave * 64 + lane) * KS;
+
+  // Scales of slice kt into slot `slot`, or (SC4) of the group that starts at
+  // slice kt into the one buffer.
+  auto issue_scales = [&](int kt, int slot) {
+    if constexpr (SC4) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(as_rsrc, MOEPD_LPTR(scales + sc_a), 16, sa_off, kt * 4, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(bs_rsrc, MOEPD_LPTR(scales + SC_A + wave * 64), 16, sb_off, kt * 4, 0,
+                                               0);
+    } else {
+      u32x4* s = scales + slot * (SC_W / 4);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(as_rsrc, MOEPD_LPTR(s + sc_a / 4), 4, sa_off, kt * 4, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(bs_rsrc, MOEPD_LPTR(s + (SC_A + wave * 64) / 4), 4, sb_off, kt * 4, 0,
+                                               0);
     }
   };
-  auto issue = [&](int kt, int slot) {
+  auto issue_a = [&](int kt, int slot) {
+    if constexpr (!SC4) issue_scales(kt, slot);
 #pragma unroll
     for (int i = 0; i < A_INS; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(&ring[slot][(wave * A_INS + i) * 64]), 16,
-                                               a_off[i] + (uint32_t)kt * BK, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(&ring_a[slot][(wave * A_INS + i) * 64]), 16,
+                                               a_off[i], kt * BK, 0, 0);
+  };
+  auto issue_b = [&](int kt, int slot) {
 #pragma unroll
     for (int i = 0; i < B_INS; ++i)
-      __builtin_amdgcn_global_load_lds(MOEPD_GPTR(b_src[i] + kt * BK),
-                                       MOEPD_LPTR(&ring[slot][A_CH + (wave * B_INS + i) * 64]), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < SC_INS; ++i)
-      __builtin_amdgcn_global_load_lds(MOEPD_GPTR(sc_src[i] + kt * 4),
-                                       MOEPD_LPTR(&ring[slot][A_CH + B_CH + sc_dst[i] / 4]), 4, 0, 0);
-  };
-  auto prologue = [&](const TileCoord& tc) {
-    set_sources(tc);
-#pragma unroll
-    for (int st = 0; st < STAGES; ++st)
-      if (st < KT) issue(st, st);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, MOEPD_LPTR(&ring_b[slot][(wave * B_INS + i) * 64]), 16,
+                                               b_off[i & 1], b_row[i] + kt * BK, 0, 0);
   };
 
   // step s of a slice: lane half h takes chunks 4s + h and 4s + 2 + h of its
@@ -429,9 +470,9 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
   v8i32 fa[2][FM], fb[2][FB];
   u32x4 sa_raw[FM], sb_raw[FB];
   uint32_t sa[FM], sb[FB];
-  auto read_frags = [&](int slot, int sub, v8i32 (&a)[FM], v8i32 (&b)[FB]) {
-    const u32x4* As = &ring[slot][0];
-    const u32x4* Bs = &ring[slot][A_CH];
+  auto read_frags = [&](int aslot, int bslot, int sub, v8i32 (&a)[FM], v8i32 (&b)[FB]) {
+    const u32x4* As = &ring_a[aslot][0];
+    const u32x4* Bs = &ring_b[bslot][0];
     const int c0 = 4 * sub + h, c1 = 4 * sub + 2 + h;
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm) {
@@ -446,21 +487,24 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
         b[nb * FN + fn] = join(Bs[r * CPR + (c0 ^ swz<64>(r))], Bs[r * CPR + (c1 ^ swz<64>(r))]);
       }
   };
-  // Scale words are read as whole 16-byte groups (4-byte LDS reads right
-  // after the DMA issue made the compiler wait for every outstanding DMA,
-  // vmcnt(0), in the K loop); the lane's word is picked when the slice
-  // starts, so the reads have the previous step's MFMAs to land.
-  auto read_scales = [&](int slot, u32x4 (&ra)[FM], u32x4 (&rb)[FB]) {
-    const u32x4* S = &ring[slot][A_CH + B_CH];
+  // SC4: a row's 16 bytes, the words of four slices.  Otherwise the 16 bytes
+  // that hold the row's word among four rows' (4-byte LDS reads right after
+  // the DMA issue made the compiler wait for every outstanding DMA, vmcnt(0),
+  // in the K loop).
+  auto read_scales = [&](int slot) {
+    const u32x4* S = SC4 ? scales : scales + slot * (SC_W / 4);
+    constexpr int SH = SC4 ? 0 : 2;
 #pragma unroll
-    for (int fm = 0; fm < FM; ++fm) ra[fm] = S[(wm * WTM + fm * 32 + (lane & 31)) >> 2];
+    for (int fm = 0; fm < FM; ++fm) sa_raw[fm] = S[(wm * WTM + fm * 32 + (lane & 31)) >> SH];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn) rb[nb * FN + fn] = S[(BM + nb * BN + wn * WTN + fn * 32 + (lane & 31)) >> 2];
+      for (int fn = 0; fn < FN; ++fn)
+        sb_raw[nb * FN + fn] = S[(SC_A + nb * BN + wn * WTN + fn * 32 + (lane & 31)) >> SH];
   };
-  auto pick = [&](const u32x4& v) {  // the lane's word (rows are multiples of 4 apart), shifted to block h
-    const int c = lane & 3;
+  // the lane's word of slice kt, shifted to block h
+  auto pick = [&](const u32x4& v, int kt) {
+    const int c = SC4 ? kt & 3 : lane & 3;
     const uint32_t w = c == 0 ? v[0] : c == 1 ? v[1] : c == 2 ? v[2] : v[3];
     return w >> (8 * h);
   };
@@ -476,12 +520,12 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
                                                                      (int)(sa[fm] >> (16 * sub)));
   };
 
-  const int L = block_tile(g);
-  if (L < 0) return;
-  yield_to_window(g.yield);
-  TileCoord tc;
-  tile_at(g, L, BM, BN, tc);
-  prologue(tc);
+  if constexpr (SC4) issue_scales(0, 0);
+#pragma unroll
+  for (int st = 0; st < SB; ++st) {
+    if (st < SA && st < KT) issue_a(st, st);
+    if (st < KT) issue_b(st, st);
+  }
 
 #pragma unroll
   for (int i = 0; i < FM; ++i)
@@ -490,48 +534,78 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  wait_slices_lgkm0<NPS, STAGES - 1>(min(STAGES - 1, KT - 1));
+  wait_rings_lgkm0<NA, B_INS, SA - 1, SB - 1>(KT - 1);
   bare_barrier();
-  read_frags(0, 0, fa[0], fb[0]);
-  read_scales(0, sa_raw, sb_raw);
+  read_frags(0, 0, 0, fa[0], fb[0]);
+  read_scales(0);
 
-  // One K slice (MODE as in the bf16 ring: 0 refills the slot, 1 has nothing
-  // left to issue, 2 is the last slice).
-  auto slice = [&](auto mode, int kt, int slot) {
-    constexpr int MODE = decltype(mode)::value;
+  // One K slice.  LAST: the tile's last slice (no barrier, nothing to read
+  // ahead).  FILL: A(kt + SA) exists.  PEND: B(kt - 1 + SB) exists and is still
+  // to go out, into the slot that slice kt - 1 freed.
+  auto slice = [&](auto last, auto fill, auto pend, int kt, int aslot, int bslot) {
+    constexpr bool LAST = decltype(last)::value, FILL = decltype(fill)::value, PEND = decltype(pend)::value;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) sa[i] = pick(sa_raw[i]);
+    for (int i = 0; i < FM; ++i) sa[i] = pick(sa_raw[i], kt);
 #pragma unroll
-    for (int j = 0; j < FB; ++j) sb[j] = pick(sb_raw[j]);
+    for (int j = 0; j < FB; ++j) sb[j] = pick(sb_raw[j], kt);
     // step 0: read step 1's fragments, multiply step 0
-    read_frags(slot, 1, fa[1], fb[1]);
+    read_frags(aslot, bslot, 1, fa[1], fb[1]);
+    if constexpr (PEND && !BNOW) issue_b(kt - 1 + SB, bslot == 0 ? SB - 1 : bslot - 1);
     mfmas(0, fa[0], fb[0]);
-    interleave<0, NMF, 0, NRD, 0>();
-    if constexpr (MODE < 2) {
-      if constexpr (MODE == 0) wait_vmcnt_lgkm0<NPS * (STAGES - 2)>();
-      else wait_slices_lgkm0<NPS, STAGES - 2>(min(STAGES - 2, KT - 2 - kt));
+    interleave<0, NMF, PEND && !BNOW ? B_INS : 0, NRD, 0>();
+    if constexpr (!LAST) {
+      if constexpr (FILL || PEND) wait_vmcnt_lgkm0<NA*(SA - 2) + B_INS * (SB - 2)>();
+      else wait_rings_lgkm0<NA, B_INS, SA - 2, SB - 2>(KT - 2 - kt);
       bare_barrier();
-      int ns = slot + 1;
-      if (ns == STAGES) ns = 0;
-      if constexpr (MODE == 0) issue(kt + STAGES, slot);
-      read_frags(ns, 0, fa[0], fb[0]);
-      read_scales(ns, sa_raw, sb_raw);
+      const int na = aslot + 1 == SA ? 0 : aslot + 1, nb = bslot + 1 == SB ? 0 : bslot + 1;
+      if constexpr (SC4) {
+        if ((kt & 3) == 0 && kt + 4 < KT) issue_scales(kt + 4, 0);
+        if ((kt & 3) == 3) read_scales(0);
+      }
+      if constexpr (FILL) {
+        issue_a(kt + SA, aslot);
+        if constexpr (BNOW) issue_b(kt + SB, bslot);
+      }
+      read_frags(na, nb, 0, fa[0], fb[0]);
+      if constexpr (!SC4) read_scales(na);
       mfmas(1, fa[1], fb[1]);
-      interleave<0, NMF, MODE == 0 ? NPS : 0, NRD + FM + FB, 1>();
+      interleave<0, NMF, FILL ? NA + (BNOW ? B_INS : 0) : 0, NRD + (SC4 ? 0 : FM + FB), 1>();
     } else {
       mfmas(1, fa[1], fb[1]);
     }
   };
-  int kt = 0, slot = 0;
-  for (; kt < KT - STAGES; ++kt) {
-    slice(std::integral_constant<int, 0>{}, kt, slot);
-    if (++slot == STAGES) slot = 0;
+  int kt = 0, aslot = 0, bslot = 0;
+  auto advance = [&] {
+    ++kt;
+    if (++aslot == SA) aslot = 0;
+    if (++bslot == SB) bslot = 0;
+  };
+  using T = std::true_type;
+  using F = std::false_type;
+  if (KT > SA) {
+    slice(F{}, T{}, F{}, kt, aslot, bslot);  // the prologue's groups went out whole
+    advance();
+    while (kt < KT - SA) {
+      slice(F{}, T{}, T{}, kt, aslot, bslot);
+      advance();
+    }
+    if constexpr (SB == SA && !BNOW) {  // B(KT - 1)
+      slice(F{}, F{}, T{}, kt, aslot, bslot);
+      advance();
+    }
   }
-  for (; kt < KT - 1; ++kt) {
-    slice(std::integral_constant<int, 1>{}, kt, slot);
-    if (++slot == STAGES) slot = 0;
+  while (kt < KT - 1) {
+    slice(F{}, F{}, F{}, kt, aslot, bslot);
+    advance();
   }
-  slice(std::integral_constant<int, 2>{}, kt, slot);
+  slice(T{}, F{}, F{}, kt, aslot, bslot);
+  // The last MFMAs, and the vector code that picks their scales, stay above
+  // the epilogue's per-row branches: under a partial EXEC mask the picks would
+  // leave the scales of weight rows on masked lanes unset.
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FB; ++j) asm volatile("" : "+a"(acc[i][j]));
 
   // epilogue (lane l: row l & 31 of each 32-row block, columns 8q + 4h + t)
 #pragma unroll
@@ -573,12 +647,49 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g) {
   }
 }
 
-__global__ __launch_bounds__(256) void gemm1_mx_prefill(GemmArgsMX g) {
-  gemm_mx_ring_body<256, 256, 2, 2, true, 2>(g);
+// A ring tile, cut to the 32-row blocks it holds: an expert's rows are shared
+// evenly among its m-tiles, and a tile's MFMAs, A transfers and fragment reads
+// all go with the rows it is built for.  Up to 160 rows the four waves stand
+// side by side along N (each reads every A fragment and its own weights'); the
+// taller tiles take a 2 x 2 grid, whose fragment reads per MFMA are fewer.  The
+// LDS that shorter tiles leave goes to more slots.  What bounds these tiles is
+// the LDS (fragment reads and DMA writes, about as many cycles as the MFMAs at
+// 160 rows) and, with few rows, the weight stream.  The DeepSeek-V3-shaped
+// share (H 7168, I 2048, 32 experts), P alone, GEMM1 / GEMM2 in us, one tile
+// of 256 rows for any number of rows -> cut to the rows:
+//   32 rows per expert   237 / 128 -> 184 / 101 (5.3 TB/s of weights in GEMM1)
+//   128                  263 / 155 -> 208 / 135
+//   256                  444 / 236 -> 317 / 204
+//   512                  616 / 365 -> 521 / 353
+// and with 47 rows per expert at H 2560, I 768 (64 experts) 90 / 50 -> 65 / 43.
+constexpr int kMxRingChunks = 160 * 1024 / 16;
+template <bool GATED, bool SC4>
+__device__ __forceinline__ void gemm_mx_ring(const GemmArgsMX& g) {
+  __shared__ u32x4 lds[kMxRingChunks];
+  const int L = block_tile(g);
+  if (L < 0) return;
+  yield_to_window(g.yield);
+  TileCoord tc;
+  tile_at(g, L, kMxMaxRows, GATED ? 128 : 256, tc);
+  const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
+#define MOEPD_MX_RING(BM, WM, WN, SA, SB, SC4)                                           \
+  do {                                                                                   \
+    static_assert(mx_ring_chunks(BM, SA, SB) <= kMxRingChunks, "ring exceeds the LDS"); \
+    gemm_mx_ring_body<BM, WM, WN, SA, SB, GATED, SC4>(g, tc, lds);                       \
+  } while (0)
+  if (blocks <= 1) MOEPD_MX_RING(32, 1, 4, 3, 4, SC4);
+  else if (blocks == 2) MOEPD_MX_RING(64, 1, 4, 3, 3, SC4);
+  else if (blocks == 3) MOEPD_MX_RING(96, 1, 4, 3, 3, SC4);
+  else if (blocks == 4) MOEPD_MX_RING(128, 1, 4, 3, 3, SC4);
+  else if (blocks == 5) MOEPD_MX_RING(160, 1, 4, 2, 3, SC4);
+  else if (blocks == 6) MOEPD_MX_RING(192, 2, 2, 2, 3, SC4);
+  else MOEPD_MX_RING(256, 2, 2, 2, 2, SC4);
+#undef MOEPD_MX_RING
 }
-__global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) {
-  gemm_mx_ring_body<256, 256, 2, 2, false, 2>(g);
-}
+template <bool SC4>
+__global__ __launch_bounds__(256) void gemm1_mx_prefill(GemmArgsMX g) { gemm_mx_ring<true, SC4>(g); }
+template <bool SC4>
+__global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) { gemm_mx_ring<false, SC4>(g); }
 
 template <bool GATED, bool SC2>
 __global__ __launch_bounds__(64 * kMxDecodeWaves) void gemm_mx_skinny(GemmArgsMX g) {
@@ -629,8 +740,11 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
   if (regime == 0) {
     g.n_tiles = gemm == 1 ? (g.N + 127) / 128 : (g.N + 255) / 256;
     const dim3 grid(round8_mx((long long)max_m_tiles * g.n_tiles));
-    if (gemm == 1) gemm1_mx_prefill<<<grid, 256, 0, s>>>(g);
-    else gemm2_mx_prefill<<<grid, 256, 0, s>>>(g);
+    // a row's scales of four slices in one aligned 16-byte gather
+    const bool sc4 = g.K % 512 == 0 && ((uintptr_t)g.As | (uintptr_t)g.Bs) % 16 == 0;
+    auto go = [&](auto k) { k<<<grid, 256, 0, s>>>(g); };
+    if (gemm == 1) sc4 ? go(gemm1_mx_prefill<true>) : go(gemm1_mx_prefill<false>);
+    else sc4 ? go(gemm2_mx_prefill<true>) : go(gemm2_mx_prefill<false>);
   } else {
     g.n_tiles = (g.N + 32 * kMxDecodeWaves - 1) / (32 * kMxDecodeWaves);
     g.xcd_local = g.n_tiles % 8 == 0 ? 2 : 1;
@@ -644,6 +758,21 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
   return hipGetLastError();
 }
 
-int ffn_mx_bm(int regime) { return regime == 0 ? 256 : 32; }
+// Rows per m-tile of the ring: an expert of r rows takes ceil(r / this) tiles.
+// 192, unless taller tiles save most experts one: an expert's rows scatter
+// about the expected count by its square root, so that is asked at one such
+// deviation above it.  A 256-row tile has room for two slots of each ring only,
+// and two tiles of half its rows take about its time, so it pays where the
+// number of tiles (and of rounds over the CUs) falls.  The share above, whole
+// layer in us, 192 / 256:  192 rows 621 / 558,  224 rows 627 / 589,
+// 256 rows 669 / 727,  320 rows 774 / 776,  384 rows 938 / 932,
+// 512 rows 1127 / 1175;  skewed 16384-token batch 5680 / 5882.
+int ffn_mx_bm(int regime, long long avg_rows) {
+  if (regime != 0) return 32;
+  long long dev = 0;
+  while ((dev + 1) * (dev + 1) <= avg_rows) ++dev;
+  const long long r = avg_rows + dev;
+  return (r + kMxMaxRows - 1) / kMxMaxRows < (r + 191) / 192 ? kMxMaxRows : 192;
+}
 
 }  // namespace moepd

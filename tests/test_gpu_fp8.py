@@ -164,3 +164,31 @@ def test_fp8_concurrent_phases_match_solo():
             assert torch.equal(g.out[ph], solo[ph]), ph
     finally:
         g.close()
+
+
+# Exact rows per expert at the edges of the ring tiles' heights: 32-row blocks,
+# one and two tiles of 192 (and, where the expected rows make the tiles taller,
+# of 256) rows; K slices from one up, with and without the four-slice scale
+# gathers (K a multiple of 512), fewer than the rings' slots, as many, and one
+# more.
+EDGE_ROWS = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 256, 257, 384, 385]
+TALL_ROWS = [193, 200, 224, 225, 255, 256, 257, 300]
+
+
+@pytest.mark.parametrize("rows,H,I", [
+    (EDGE_ROWS, 128, 256), (EDGE_ROWS, 384, 512), (EDGE_ROWS, 512, 640), (EDGE_ROWS, 1024, 384),
+    (TALL_ROWS, 512, 128), (TALL_ROWS, 640, 1536),
+], ids=lambda v: f"{v[0]}-{v[-1]}" if isinstance(v, list) else str(v))
+def test_fp8_ring_heights(rows, H, I):
+    E, T = len(rows), sum(rows)
+    spec = LayerSpec("rows-fp8", E=E, e0=0, E_loc=E, k=1, H=H, I=I, dtype=FP8, T_P=T, T_D=0)
+    inp = make_layer(spec, seed=43)
+    owner = np.random.default_rng(44).permutation(np.repeat(np.arange(E), rows))
+    inp.logits[0] = np.where(np.arange(E)[None, :] == owner[:, None], 1.0, -1.0).astype(np.float32)
+    g = GpuLayer(inp)
+    try:
+        g.run(0)
+        check_phase(g, inp, 0)
+        assert g.fetch(0)["counts"].tolist() == rows
+    finally:
+        g.close()

@@ -68,7 +68,7 @@ struct moe_ctx {
   Phase ph[MOE_NUM_PHASES];
   // Tile regime of each phase's latest bf16 expert-FFN launch (-1: none).
   // The other phase reads it (possibly from another host thread) to choose
-  // its decode tiles: 160-row prefill tiles leave 4 KB of a CU's LDS free,
+  // its decode tiles: prefill tiles leave 3 KB of a CU's LDS free,
   // too little for the LDS-staged decode tile, so beside them the phase takes
   // the tile that needs no LDS and can share their CUs.  Only a performance
   // choice: both tiles give the same results.
@@ -274,8 +274,8 @@ int layout(moe_ctx* ctx, Phase& p, hipStream_t stream) {
     p.bm = ffn_mx_bm(p.regime, avg);
   } else if (c.dtype == MOE_DTYPE_BF16) {
     // Rows per resident expert expected under even routing: T*k/E.  Small
-    // batches stream weights (32-row tiles); large ones take 160-row tiles,
-    // and very large ones 256-row tiles, which move fewer bytes into LDS per
+    // batches stream weights (32-row tiles); large ones take tiles of up to 192
+    // rows, and very large ones 256-row tiles, which move fewer bytes into LDS per
     // flop.
     const long long avg = (long long)T * k / c.num_experts;
     p.regime = avg >= 512 ? 2 : avg >= 32 ? 0 : 1;

@@ -23,21 +23,19 @@
 //    one slice ahead; GEMM2 also has a share form in 32-deep slices that
 //    leaves a CU room for the other phase's decode tiles (gemm_ring_body and
 //    the kernels below);
-//  * large batches (prefill): 256 threads, 160 x (128 gate + 128 up) or
-//    160 x 256 output tiles, 32x32x16 MFMAs, the four waves side by side
-//    along N.  Operands stream HBM -> LDS with global_load_lds_dwordx4 into a
-//    ring of three 64-deep K slices (156 KB); fragments are double-buffered
-//    in registers and the LDS reads and DMA issues are interleaved with the
-//    MFMAs (see gemm_ring_body).  160 rows, where 128 would be the plain
-//    choice, because an expert's rows are shared evenly among its m-tiles:
-//    with a few hundred rows per expert, ceil(rows / 160) saves the third,
-//    mostly empty m-tile that ceil(rows / 128) adds whenever an expert holds
-//    a little more than 256 rows, and every m-tile re-streams the weights;
+//  * large batches (prefill): 256 threads, tiles of up to 192 rows x (128 gate
+//    + 128 up) or 256 columns, cut to the 32-row blocks they hold, 32x32x16
+//    MFMAs; up to 160 rows the four waves stand side by side along N.
+//    Operands stream HBM -> LDS by 16-byte DMA into rings of 64-deep K slices
+//    (157 KB); fragments are double-buffered in registers and the LDS reads
+//    and DMA issues are placed between the MFMAs (see gemm_ring_body).  An
+//    expert's rows are shared evenly among its ceil(rows / 192) m-tiles, each
+//    of which streams the expert's weights once more;
 //  * small batches (decode, a few rows per expert): the layer is a weight
 //    stream, one 32-row m-tile and 32 columns per single-wave workgroup,
 //    two 64-deep K blocks in flight.  Each block is loaded with whole-line
 //    reads and transposed through the wave's own 12 KB LDS stage into MFMA
-//    operand layout; beside the other phase's 160-row prefill tiles (which
+//    operand layout; beside the other phase's prefill tiles (which
 //    leave 4 KB of LDS) the tile loads straight into operand registers
 //    instead, with no LDS, so it can share their CUs.
 #include <type_traits>
@@ -218,7 +216,7 @@ __device__ __forceinline__ void gemm_skinny_tile(const GemmArgs& g, const TileCo
 
 // The same tile with each operand loaded straight into MFMA lane layout (16
 // bytes from each of 32 rows per instruction) and no LDS: slower alone, but
-// it fits on a CU beside a 160-row prefill tile of the other phase, whose
+// it fits on a CU beside a prefill tile of the other phase, whose
 // ring leaves 4 KB of LDS free.
 template <bool GATED, bool ROT>
 __device__ __forceinline__ void gemm_skinny_tile_direct(const GemmArgs& g, const TileCoord& tc) {
@@ -322,9 +320,9 @@ __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
 //  * fragments: each 16-deep substep's A/B fragments are read from LDS into
 //    one of two register sets while the MFMAs of the previous substep run on
 //    the other (the read of a slice's first substep crosses the barrier);
-//  * instructions: scheduling-group barriers spread the LDS reads and DMA
-//    issues between the MFMAs, so the single wave per SIMD never waits on
-//    its own reads.
+//  * instructions: each substep's LDS reads and DMA issues stand between its
+//    MFMAs in a fixed order (weave), so the single wave per SIMD never waits
+//    on its own reads.
 //
 // Wave (wm, wn) of the WM x WN wave grid owns rows [wm WTM, +WTM) and output
 // columns [wn WTN, +WTN) (for GATED, the gate and the up column of the same
@@ -360,18 +358,26 @@ __device__ __forceinline__ int read_window_cell(const void* cell) {
 }
 constexpr int kCachePolicyAgent = 0x10;  // sc1: coherent at agent scope
 
-// STAGES slots hold weight slices; SA >= STAGES slots hold activation
-// slices.  With SA = STAGES + 1 (two weight slots only) the activation
-// slices run one slice further ahead than the weight slices: the slice end
-// that issues B(j) is followed, over the next slice's substeps, by A(j + 1),
-// so the counted wait at a slice end retires the next slice's weights while
-// that slice's activations, issued a slice earlier, have had up to two
-// slices' time to land.  WIN: the tile keeps the LDS cells of the D window
-// word (tiles that never yield leave them out, which frees the LDS for the
-// third activation slot).
-template <int BM, int BR, int BK, int WM, int WN, bool GATED, int STAGES, bool DENSE = false, int SA = STAGES,
-          bool WIN = true>
-__device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
+// STAGES slots hold weight slices, SA slots hold activation slices.  With SA
+// = STAGES + 1 (two weight slots only) the activation slices run one slice
+// further ahead than the weight slices: the slice end that issues B(j) is
+// followed, over the next slice's substeps, by A(j + 1), so the counted wait
+// at a slice end retires the next slice's weights while that slice's
+// activations, issued a slice earlier, have had up to two slices' time to
+// land.  With SA = STAGES - 1 it is the weights that run ahead: A(j) goes out
+// whole at the slice end, then B(j + 1) over the next slice's substeps.  WIN:
+// the tile keeps the LDS cells of the D window word (tiles that never yield
+// leave them out, which frees the LDS for the third activation slot).
+//
+// One LDS object holds the activation and weight rings of K slices, then
+// (WIN) the cells of the D window word (its first word in each cell, see
+// load_window).
+constexpr int ring_chunks(int bm, int br, int bk, int sa, int sb, bool win) {
+  return (sa * bm + sb * br) * (bk / 8) + (win ? 64 : 0);
+}
+
+template <int BM, int BR, int BK, int WM, int WN, bool GATED, int STAGES, bool DENSE, int SA, bool WIN>
+__device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoord& tc, u32x4* lds, int wait_budget) {
   constexpr int NB = GATED ? 2 : 1;
   constexpr int BN = BR / NB;
   constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -390,7 +396,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   static_assert(FM * 32 == WTM && FN * 32 == WTN, "wave tile must be a multiple of 32x32");
   static_assert(STAGES >= 2 && NPS * (STAGES - 1) < 64, "pipeline depth");
   constexpr int LEAD = SA - STAGES;  // slices the activations run ahead of the weights
-  static_assert(LEAD == 0 || (LEAD == 1 && STAGES == 2 && !WIN && !DENSE), "activation lead: two weight slots only");
+  static_assert(LEAD == 0 || (LEAD == 1 && STAGES == 2 && !WIN && !DENSE) || (LEAD == -1 && SA >= 2),
+                "activation lead: two weight slots only");
   // The DMA group a slice end would issue goes out in parts, so the
   // vector-memory queue takes a part at a time beside the MFMAs instead of
   // the whole group at once.  Without the lead the group's NPS instructions
@@ -398,23 +405,16 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   // of the next slice (into the slot the barrier freed).  With it the
   // weights (one slice to land) go out whole at the slice end and the
   // activations' A_INS make SUB - 1 parts, one per substep of the next slice
-  // but its last (their slot too was freed a barrier earlier).
-  constexpr int PART_N = LEAD == 1 ? A_INS : NPS;       // instructions cut into parts
-  constexpr int NPART = LEAD == 1 ? SUB - 1 : SUB;      // parts
+  // but its last (their slot too was freed a barrier earlier).  With the
+  // weights ahead it is the other way round.
+  constexpr int PART_N = LEAD == 1 ? A_INS : LEAD == -1 ? B_INS : NPS;  // instructions cut into parts
+  constexpr int NPART = LEAD != 0 ? SUB - 1 : SUB;                      // parts
   constexpr int END_PARTS = NPART - (SUB - 1);         // parts issued at the slice end (0 or 1)
   constexpr int PART0 = END_PARTS * PART_N / NPART;     // instructions among them
   static_assert(2 * A_INS + B_INS < 64, "prologue wait range");
-  // One LDS object: the activation and weight rings of K slices, then (WIN)
-  // the cells of the D window word (its first word in each cell, see
-  // load_window).
-  struct LdsRings {
-    u32x4 a[SA][A_CH];
-    u32x4 b[STAGES][B_CH];
-  };
-  struct LdsWin : LdsRings {
-    u32x4 window[64];
-  };
-  __shared__ std::conditional_t<WIN, LdsWin, LdsRings> lds;
+  u32x4(*const ring_a)[A_CH] = reinterpret_cast<u32x4(*)[A_CH]>(lds);
+  u32x4(*const ring_b)[B_CH] = reinterpret_cast<u32x4(*)[B_CH]>(lds + SA * A_CH);
+  u32x4* const window = lds + SA * A_CH + STAGES * B_CH;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -426,42 +426,52 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   // chunk (l % CPR) ^ swz(r).
   const int lrow = lane / CPR, lphys = lane % CPR;
 
-  // A rows are read through a buffer resource that covers exactly the
-  // tile's rows of its expert: rows past the expert's end fall outside it,
-  // so their loads return zeros and make no memory request (the output rows
-  // they feed are never stored).  B rows past N are clamped to the last.
-  __amdgpu_buffer_rsrc_t a_rsrc;
-  uint32_t a_off[A_INS];  // byte offset of each A instruction's row chunk
-  const uint16_t* b_src[B_INS];
-  auto set_sources = [&](const TileCoord& tc) {
-    const int m0 = __builtin_amdgcn_readfirstlane(tc.m0);
-    const int rows = min(__builtin_amdgcn_readfirstlane(tc.m_end) - m0, BM);
-    a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(g.A + (size_t)m0 * g.K), (short)0, rows * g.K * 2,
-                                               kBufferRsrcWord3);
-    const uint16_t* Be = g.B + (size_t)__builtin_amdgcn_readfirstlane(tc.e) * g.b_stride;
-    // first K element of the tile's run (a dense split starts further in)
-    const int k0 = DENSE ? __builtin_amdgcn_readfirstlane(tc.split) * g.dense_ks * BK : 0;
+  // Both operands are read through buffer resources with 32-bit lane offsets;
+  // the K offset (and the weights' row group) goes in the scalar offset, so an
+  // issue takes no vector instruction.  A's resource covers exactly the
+  // tile's rows of its expert: rows past the expert's end fall outside it, so
+  // their loads return zeros and make no memory request (the output rows they
+  // feed are never stored).  Weight rows past N read the last ones: per lane
+  // in the dense mode, else (N a multiple of 64) per group of RPI rows.
+  const int m0 = __builtin_amdgcn_readfirstlane(tc.m0);
+  const int n0 = __builtin_amdgcn_readfirstlane(tc.n0);
+  const int rows = min(__builtin_amdgcn_readfirstlane(tc.m_end) - m0, BM);
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(g.A + (size_t)m0 * g.K), (short)0, rows * g.K * 2, kBufferRsrcWord3);
+  const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(g.B + (size_t)__builtin_amdgcn_readfirstlane(tc.e) * g.b_stride), (short)0,
+      (GATED ? g.up_row + g.N : g.N) * g.K * 2, kBufferRsrcWord3);
+  // first K element of the tile's run (a dense split starts further in)
+  const int k0 = DENSE ? __builtin_amdgcn_readfirstlane(tc.split) * g.dense_ks * BK : 0;
+  // The swizzle of staged row r = RPI (wave INS + i) + lrow depends on r modulo
+  // 16 alone, so two lane offsets serve all of B's groups.
+  int a_off[A_INS], b_off[DENSE ? B_INS : 2], b_row[B_INS];
 #pragma unroll
-    for (int i = 0; i < A_INS; ++i) {
-      const int r = (wave * A_INS + i) * RPI + lrow;
-      a_off[i] = (uint32_t)(r * g.K + k0 + (lphys ^ swz<BK>(r)) * 8) * 2u;
-    }
+  for (int i = 0; i < A_INS; ++i) {
+    const int r = (wave * A_INS + i) * RPI + lrow;
+    a_off[i] = (r * g.K + (lphys ^ swz<BK>(r)) * 8) * 2;
+  }
 #pragma unroll
-    for (int i = 0; i < B_INS; ++i) {
-      const int r = (wave * B_INS + i) * RPI + lrow;
+  for (int i = 0; i < B_INS; ++i) {
+    const int r = (wave * B_INS + i) * RPI;
+    if constexpr (DENSE) {
+      b_row[i] = 0;
+      b_off[i] = (min(n0 + r + lrow, g.N - 1) * g.K + (lphys ^ swz<BK>(r + lrow)) * 8) * 2;
+    } else {
       int brow;
-      if (GATED) brow = r < BN ? min(tc.n0 + r, g.N - 1) : g.up_row + min(tc.n0 + r - BN, g.N - 1);
-      else brow = min(tc.n0 + r, g.N - 1);
-      b_src[i] = Be + (size_t)brow * g.K + k0 + (lphys ^ swz<BK>(r)) * 8;
+      if (GATED) brow = r < BN ? min(n0 + r, g.N - RPI) : g.up_row + min(n0 + r - BN, g.N - RPI);
+      else brow = min(n0 + r, g.N - RPI);
+      b_row[i] = __builtin_amdgcn_readfirstlane(brow) * g.K * 2;
+      if (i < 2) b_off[i] = (lrow * g.K + (lphys ^ swz<BK>(r + lrow)) * 8) * 2;
     }
-  };
+  }
   auto issue_a1 = [&](int i, int koff, int slot) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(&lds.a[slot][(wave * A_INS + i) * 64]), 16,
-                                             a_off[i] + (uint32_t)koff * 2u, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(&ring_a[slot][(wave * A_INS + i) * 64]), 16, a_off[i],
+                                             (k0 + koff) * 2, 0, 0);
   };
   auto issue_b1 = [&](int i, int koff, int slot) {
-    __builtin_amdgcn_global_load_lds(MOEPD_GPTR(b_src[i] + koff), MOEPD_LPTR(&lds.b[slot][(wave * B_INS + i) * 64]), 16,
-                                     0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, MOEPD_LPTR(&ring_b[slot][(wave * B_INS + i) * 64]), 16,
+                                             b_off[DENSE ? i : i & 1], b_row[i] + (k0 + koff) * 2, 0, 0);
   };
   auto issue_a = [&](int kt, int slot) {
 #pragma unroll
@@ -471,61 +481,31 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
 #pragma unroll
     for (int i = 0; i < B_INS; ++i) issue_b1(i, kt * BK, slot);
   };
-  // Part p of slice kt's spread DMA into slot `slot`: instructions
-  // [PART_N p / NPART, PART_N (p + 1) / NPART) of A's A_INS then B's B_INS
-  // (with the lead, of A's alone).  p is a constant once the loops around a
-  // call are unrolled, and so is every branch here.
-  auto issue_part = [&](int kt, int slot, int p) {
-#pragma unroll
-    for (int i = PART_N * p / NPART; i < PART_N * (p + 1) / NPART; ++i) {
-      if (LEAD == 1 || i < A_INS) issue_a1(i, kt * BK, slot);
-      else issue_b1(i - A_INS, kt * BK, slot);
-    }
-  };
-  // DMA group of slice j, whole (the prologue's): without a lead, A(j) then
-  // B(j) into slot j % STAGES; with the activation lead, B(j) into weight
-  // slot j % 2, then A(j + 1) (if the tile has it) into activation slot
-  // (j + 1) % 3.
-  auto issue = [&](int kt, int bslot, int aslot_next) {
-    if constexpr (LEAD == 0) {
-      issue_a(kt, bslot);
-      issue_b(kt, bslot);
-    } else {
-      issue_b(kt, bslot);
-      if (kt + 1 < KT) issue_a(kt + 1, aslot_next);
-    }
+  // Instruction i of slice kt's spread DMA into slot `slot`: of A's A_INS then
+  // B's B_INS, or with a lead of the leading operand's alone.  Part p of it is
+  // [PART_N p / NPART, PART_N (p + 1) / NPART).
+  auto issue_part1 = [&](int i, int kt, int slot) {
+    if (LEAD == -1) issue_b1(i, kt * BK, slot);
+    else if (LEAD == 1 || i < A_INS) issue_a1(i, kt * BK, slot);
+    else issue_b1(i - A_INS, kt * BK, slot);
   };
   auto load_window = [&] {
     if constexpr (WIN)
-      __builtin_amdgcn_global_load_lds(MOEPD_GPTR(g.yield.word), MOEPD_LPTR(&lds.window[0]), 16, 0,
+      __builtin_amdgcn_global_load_lds(MOEPD_GPTR(g.yield.word), MOEPD_LPTR(window), 16, 0,
                                        kCachePolicyAgent);
   };
-  auto prologue = [&](const TileCoord& tc) {
-    set_sources(tc);
-    if constexpr (LEAD == 1) issue_a(0, 0);
-#pragma unroll
-    for (int st = 0; st < STAGES; ++st)
-      if (st < KT) issue(st, st, st + 1);
-    if (WIN && g.yield.word) load_window();
-  };
-
   bf16x8_t fa[2][FM], fb[2][FB];
-  auto read_frags = [&](int aslot, int bslot, int sub, bf16x8_t (&a)[FM], bf16x8_t (&b)[FB]) {
-    const u32x4* As = &lds.a[aslot][0];
-    const u32x4* Bs = &lds.b[bslot][0];
+  // Fragment i of substep `sub`: A's FM row blocks, then B's FB column blocks
+  // (gate, up).
+  auto read_frag = [&](int i, int aslot, int bslot, int sub, bf16x8_t (&a)[FM], bf16x8_t (&b)[FB]) {
     const int ch = 2 * sub + (lane >> 5);
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-      const int r = wm * WTM + fm * 32 + (lane & 31);
-      a[fm] = as_bf16x8(As[r * CPR + (ch ^ swz<BK>(r))]);
+    if (i < FM) {
+      const int r = wm * WTM + i * 32 + (lane & 31);
+      a[i] = as_bf16x8(ring_a[aslot][r * CPR + (ch ^ swz<BK>(r))]);
+    } else {
+      const int j = i - FM, r = j / FN * BN + wn * WTN + j % FN * 32 + (lane & 31);
+      b[j] = as_bf16x8(ring_b[bslot][r * CPR + (ch ^ swz<BK>(r))]);
     }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
-        const int r = nb * BN + wn * WTN + fn * 32 + (lane & 31);
-        b[nb * FN + fn] = as_bf16x8(Bs[r * CPR + (ch ^ swz<BK>(r))]);
-      }
   };
 
   // The MFMAs take the weight fragment as their first operand, so each
@@ -533,49 +513,25 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   // (l & 31) and, in registers 4q..4q+3, the four consecutive columns
   // 8q + 4 (l >> 5) + 0..3 (see the epilogue's vector stores).
   f32x16_t acc[FM][FB];
-  auto mfmas = [&](const bf16x8_t (&a)[FM], const bf16x8_t (&b)[FB]) {
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-      for (int j = 0; j < FB; ++j) acc[fm][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[fm], acc[fm][j], 0, 0, 0);
+  auto mfma = [&](int i, const bf16x8_t (&a)[FM], const bf16x8_t (&b)[FB]) {
+    const int fm = i / FB, j = i % FB;
+    acc[fm][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[fm], acc[fm][j], 0, 0, 0);
   };
+  auto no_op = [](auto) {};
 
-  const int L = block_tile<DENSE>(g);
-  if (L < 0) return;
-  // Hand-over pair: one thread decides for the workgroup (whether the other
-  // phase has a layer in flight now, or whether the first launch did this
-  // tile) and passes the decision through the ring's first LDS word, which no
-  // DMA has touched yet, so every wave leaves or stays together.
-  constexpr bool HANDOFF = !GATED && !DENSE && BM == 256;
-  if constexpr (HANDOFF) {
-    if (g.handoff) {
-      int* cell = reinterpret_cast<int*>(&lds);
-      if (threadIdx.x == 0) {
-        int skip;
-        if (g.handoff == 1) {
-          skip = __hip_atomic_load(g.window, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-        } else {
-          skip = g.tile_done[L];
-          if (skip) g.tile_done[L] = 0;
-        }
-        *cell = skip;
-      }
-      __syncthreads();
-      const int skip = *cell;
-      __syncthreads();  // every wave has read the word before the ring's DMA lands
-      if (skip) return;
-    }
+  if constexpr (DENSE) KT = min(g.dense_ks, KT - tc.split * g.dense_ks);
+  // The prologue's groups go out whole, in the order of the K loop's queue:
+  // without a lead, or with the weights ahead, A(j) then B(j); with the
+  // activation lead B(j) then A(j + 1).
+  if constexpr (LEAD == 1) issue_a(0, 0);
+#pragma unroll
+  for (int st = 0; st < STAGES; ++st) {
+    if (st >= KT) break;
+    if (LEAD <= 0 && st < SA) issue_a(st, st);
+    issue_b(st, st);
+    if (LEAD == 1 && st + 1 < KT) issue_a(st + 1, st + 1);
   }
-  int wait_budget = g.yield.polls;  // shared by the tile's start and in-tile waits
-  yield_to_window(g.yield, wait_budget);
-  TileCoord tc;
-  if constexpr (DENSE) {
-    dense_tile_at(g, L, BM, BN, tc);
-    KT = min(g.dense_ks, KT - tc.split * g.dense_ks);
-  } else {
-    tile_at(g, L, BM, BN, tc);
-  }
-  prologue(tc);
+  if (WIN && g.yield.word) load_window();
 
 #pragma unroll
   for (int i = 0; i < FM; ++i)
@@ -586,16 +542,18 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
 
   // Slice 0 has landed once at most min(STAGES - 1, KT - 1) newer slices
   // remain; with the activation lead, once at most A(1), B(1) and A(2) (those
-  // the tile has) remain behind B(0).
-  if constexpr (LEAD == 0) {
-    wait_slices_lgkm0<NPS, STAGES - 1>(min(STAGES - 1, KT - 1));
+  // the tile has) remain behind B(0); with the weights ahead, once at most the
+  // newer slices of either ring remain.
+  if constexpr (LEAD <= 0) {
+    wait_rings_lgkm0<A_INS, B_INS, SA - 1, STAGES - 1>(KT - 1);
   } else {
     if (KT > 2) wait_vmcnt_lgkm0<2 * A_INS + B_INS>();
     else if (KT == 2) wait_vmcnt_lgkm0<A_INS + B_INS>();
     else wait_vmcnt_lgkm0<0>();
   }
   bare_barrier();
-  read_frags(0, 0, 0, fa[0], fb[0]);
+#pragma unroll
+  for (int i = 0; i < NRD; ++i) read_frag(i, 0, 0, 0, fa[0], fb[0]);
 
   // One K slice.  MODE 0: slice kt + STAGES is issued into this slot after
   // the barrier; MODE 1: no slices left to issue; MODE 2: the tile's last
@@ -612,18 +570,19 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
     if constexpr (LEAD == 1) {
       pkt = kt + 2;
       pslot = aslot + 2 >= SA ? aslot + 2 - SA : aslot + 2;
-    } else {
+    } else {  // also the slice and slot of B with the weights ahead
       pkt = kt - 1 + STAGES;
       pslot = bslot == 0 ? STAGES - 1 : bslot - 1;
     }
-#pragma unroll
-    for (int sub = 0; sub < SUB; ++sub) {
-      const int cur = sub & 1, nxt = cur ^ 1;
-      if (sub + 1 < SUB) {
-        read_frags(aslot, bslot, sub + 1, fa[nxt], fb[nxt]);
-        if constexpr (PEND) issue_part(pkt, pslot, END_PARTS + sub);
-        mfmas(fa[cur], fb[cur]);
-        interleave<0, NMF, PEND ? (PART_N + NPART - 1) / NPART : 0, NRD, 0>();
+    weave_run<0, SUB>([&](auto subc) {
+      constexpr int sub = decltype(subc)::value;
+      constexpr int cur = sub & 1, nxt = cur ^ 1;
+      auto mul = [&](auto i) { mfma(i, fa[cur], fb[cur]); };
+      if constexpr (sub + 1 < SUB) {
+        auto rd = [&](auto i) { read_frag(i, aslot, bslot, sub + 1, fa[nxt], fb[nxt]); };
+        constexpr int P = END_PARTS + sub;
+        constexpr int D0 = PEND ? PART_N * P / NPART : 0, D1 = PEND ? PART_N * (P + 1) / NPART : 0;
+        weave<NMF, NRD, D1 - D0>(mul, rd, [&](auto i) { issue_part1(D0 + i, pkt, pslot); });
       } else if constexpr (MODE < 2) {
         // Every read of this slot is in registers once lgkmcnt is 0.  Slice
         // kt + 1 has landed once at most min(STAGES - 2, KT - 2 - kt) newer
@@ -635,17 +594,15 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
           if (kt + 2 < KT) wait_vmcnt_lgkm0<A_INS>();
           else wait_vmcnt_lgkm0<0>();
         } else if constexpr (MODE == 0) {
-          wait_vmcnt_lgkm0<NPS * (STAGES - 2)>();
+          wait_vmcnt_lgkm0<A_INS*(SA - 2) + B_INS * (STAGES - 2)>();
         } else {
-          wait_slices_lgkm0<NPS, STAGES - 2>(min(STAGES - 2, KT - 2 - kt));
+          wait_rings_lgkm0<A_INS, B_INS, SA - 2, STAGES - 2>(KT - 2 - kt);
         }
         bare_barrier();
         int nb = bslot + 1, na = aslot + 1;
         if (nb == STAGES) nb = 0;
         if (na == SA) na = 0;
         if constexpr (MODE == 0) {
-          if constexpr (LEAD == 1) issue_b(kt + STAGES, bslot);
-          else issue_part(kt + STAGES, bslot, 0);
           // D first inside a tile: every kPauseEvery slices, a P tile that
           // found the D window open at the previous check (or at the tile's
           // start) pauses until it closes (within the tile's wait budget), so
@@ -655,19 +612,23 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
           // completes before the next load into the same words is issued.
           if constexpr (WIN) {
             if (g.yield.word && (kt & (kPauseEvery - 1)) == kPauseEvery - 1) {
-              const int seen = __builtin_amdgcn_readfirstlane(read_window_cell(&lds.window[lane]));
+              const int seen = __builtin_amdgcn_readfirstlane(read_window_cell(&window[lane]));
               if (seen == g.yield.gen) yield_to_window(g.yield, wait_budget);
               load_window();
             }
           }
         }
-        read_frags(na, nb, 0, fa[nxt], fb[nxt]);
-        mfmas(fa[cur], fb[cur]);
-        interleave<0, NMF, MODE == 0 ? (LEAD == 1 ? B_INS : PART0) : 0, NRD, 1>();
+        auto rd = [&](auto i) { read_frag(i, na, nb, 0, fa[nxt], fb[nxt]); };
+        constexpr int ND = MODE != 0 ? 0 : LEAD == 1 ? B_INS : LEAD == -1 ? A_INS : PART0;
+        weave<NMF, NRD, ND>(mul, rd, [&](auto i) {
+          if constexpr (LEAD == 1) issue_b1(i, (kt + STAGES) * BK, bslot);
+          else if constexpr (LEAD == -1) issue_a1(i, (kt + SA) * BK, aslot);
+          else issue_part1(i, kt + STAGES, bslot);
+        });
       } else {
-        mfmas(fa[cur], fb[cur]);
+        weave<NMF, 0, 0>(mul, no_op, no_op);
       }
-    }
+    });
   };
   int kt = 0, aslot = 0, bslot = 0;
   auto advance = [&] {
@@ -678,11 +639,12 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   using M1 = std::integral_constant<int, 1>;
   using NoPend = std::false_type;
   using Pend = std::true_type;
-  if (KT > STAGES) {
+  constexpr int REFILL = LEAD == -1 ? SA : STAGES;  // a slice end refills for slice kt + REFILL
+  if (KT > REFILL) {
     // the prologue issued its groups whole: nothing pending in slice 0
     slice(M0{}, NoPend{}, kt, aslot, bslot);
     advance();
-    for (++kt; kt < KT - STAGES; ++kt) {
+    for (++kt; kt < KT - REFILL; ++kt) {
       slice(M0{}, Pend{}, kt, aslot, bslot);
       advance();
     }
@@ -711,7 +673,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   // Within a wave LDS operations complete in order, so a block's read-back
   // sees its writes and the next round's writes follow this round's reads.
   constexpr int NBLK = FM * FN;                                   // 32 x 32 blocks per wave
-  constexpr int STAGE_BLK = sizeof(lds) / (4 * 4096);            // blocks one wave can stage
+  constexpr int STAGE_BLK = ring_chunks(BM, BR, BK, SA, STAGES, WIN) / (4 * 256);  // blocks one wave can stage
   constexpr int EPI_BLK = NBLK < STAGE_BLK ? NBLK : STAGE_BLK;   // per round (the last may hold fewer)
   constexpr bool STAGED_Y = !GATED && !DENSE && EPI_BLK > 0;
   if constexpr (STAGED_Y) {
@@ -719,7 +681,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
     // already 0 after the last slice) before any wave overwrites it
     wait_vmcnt_lgkm0<63>();
     bare_barrier();
-    u32x4* stage = reinterpret_cast<u32x4*>(&lds) + wave * (EPI_BLK * 256);
+    u32x4* stage = lds + wave * (EPI_BLK * 256);
     const int wr = lane & 31, wh = lane >> 5;  // accumulator row, column half
     const int rr0 = lane >> 3, rc = lane & 7;  // read-back row (of 8), chunk
 #pragma unroll
@@ -747,9 +709,6 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
             *reinterpret_cast<u32x4*>(static_cast<float*>(g.C) + (size_t)row * g.N + col0 + 4 * rc) = v;
         }
       }
-    }
-    if constexpr (HANDOFF) {
-      if (g.handoff == 1 && threadIdx.x == 0) g.tile_done[L] = 1;
     }
     return;
   }
@@ -800,12 +759,99 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g) {
   }
 }
 
+// The router's tiles: 64 rows x 128 experts of one K run.
+__device__ __forceinline__ void gemm_ring_dense(const GemmArgs& g) {
+  __shared__ u32x4 lds[ring_chunks(64, 128, 64, 3, 3, true)];
+  const int L = block_tile<true>(g);
+  if (L < 0) return;
+  int wait_budget = g.yield.polls;
+  yield_to_window(g.yield, wait_budget);
+  TileCoord tc;
+  dense_tile_at(g, L, 64, 128, tc);
+  gemm_ring_body<64, 128, 64, 2, 2, false, 3, true, 3, true>(g, tc, lds, wait_budget);
+}
+
+// The 256-row tiles in BK-deep slices: two weight slots, three activation
+// slots.
+template <bool GATED, int BK>
+__device__ __forceinline__ void gemm_ring_wide(const GemmArgs& g) {
+  __shared__ u32x4 lds[ring_chunks(256, 256, BK, 3, 2, false)];
+  const int L = block_tile(g);
+  if (L < 0) return;
+  // Hand-over pair: one thread decides for the workgroup (whether the other
+  // phase has a layer in flight now, or whether the first launch did this
+  // tile) and passes the decision through the ring's first LDS word, which no
+  // DMA has touched yet, so every wave leaves or stays together.
+  if constexpr (!GATED) {
+    if (g.handoff) {
+      int* cell = reinterpret_cast<int*>(lds);
+      if (threadIdx.x == 0) {
+        int skip;
+        if (g.handoff == 1) {
+          skip = __hip_atomic_load(g.window, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        } else {
+          skip = g.tile_done[L];
+          if (skip) g.tile_done[L] = 0;
+        }
+        *cell = skip;
+      }
+      __syncthreads();
+      const int skip = *cell;
+      __syncthreads();  // every wave has read the word before the ring's DMA lands
+      if (skip) return;
+    }
+  }
+  TileCoord tc;
+  tile_at(g, L, 256, GATED ? 128 : 256, tc);
+  gemm_ring_body<256, 256, BK, 2, 2, GATED, 2, false, 3, false>(g, tc, lds, 0);
+  if constexpr (!GATED) {
+    if (g.handoff == 1 && threadIdx.x == 0) g.tile_done[L] = 1;
+  }
+}
+
+// Prefill tiles of up to 192 rows, cut to the 32-row blocks they hold: the
+// MFMAs, A transfers and fragment reads go with a tile's rows.  Six blocks take
+// a 2 x 2 grid of waves, whose fragment reads per MFMA are fewer, and two
+// activation slots, which is what the LDS leaves beside three weight slots;
+// the weights then run a slice ahead.  All of them leave a SIMD the 176
+// registers of the other phase's register-direct decode waves.  What bounds
+// them is LDS bandwidth, about as many cycles as the MFMAs, and, with few rows,
+// the weight stream.  DeepSeek-V3-shaped share (H 7168, I 2048, 32 experts), P
+// alone, whole layer in us, 160-row tiles of full height -> these: 32 rows per
+// expert 568 -> 550, 128 rows 691 -> 677, 192 rows 983 -> 905, 256 rows 1057 ->
+// 1010 (GEMM2 327 -> 306).
+constexpr int kPrefillRows = 192;
+constexpr int kPrefillChunks = ring_chunks(160, 256, 64, 3, 3, true);
+template <bool GATED>
+__device__ __forceinline__ void gemm_ring_prefill(const GemmArgs& g) {
+  __shared__ u32x4 lds[kPrefillChunks];
+  const int L = block_tile(g);
+  if (L < 0) return;
+  int wait_budget = g.yield.polls;  // shared by the tile's start and in-tile waits
+  yield_to_window(g.yield, wait_budget);
+  TileCoord tc;
+  tile_at(g, L, kPrefillRows, GATED ? 128 : 256, tc);
+  const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
+#define MOEPD_RING(BM, WM, WN, SA, SB)                                                                      \
+  do {                                                                                                      \
+    static_assert(ring_chunks(BM, 256, 64, SA, SB, true) <= kPrefillChunks, "ring exceeds the LDS");        \
+    gemm_ring_body<BM, 256, 64, WM, WN, GATED, SB, false, SA, true>(g, tc, lds, wait_budget);               \
+  } while (0)
+  if (blocks <= 1) MOEPD_RING(32, 1, 4, 3, 3);
+  else if (blocks == 2) MOEPD_RING(64, 1, 4, 3, 3);
+  else if (blocks == 3) MOEPD_RING(96, 1, 4, 3, 3);
+  else if (blocks == 4) MOEPD_RING(128, 1, 4, 3, 3);
+  else if (blocks == 5) MOEPD_RING(160, 1, 4, 3, 3);
+  else MOEPD_RING(192, 2, 2, 2, 3);
+#undef MOEPD_RING
+}
+
 // Distinct entry points so that profiles name each GEMM of each regime.
-__global__ __launch_bounds__(256) void gemm1_swiglu_prefill(GemmArgs g) { gemm_ring_body<160, 256, 64, 1, 4, true, 3>(g); }
-__global__ __launch_bounds__(256) void gemm2_down_prefill(GemmArgs g) { gemm_ring_body<160, 256, 64, 1, 4, false, 3>(g); }
+__global__ __launch_bounds__(256) void gemm1_swiglu_prefill(GemmArgs g) { gemm_ring_prefill<true>(g); }
+__global__ __launch_bounds__(256) void gemm2_down_prefill(GemmArgs g) { gemm_ring_prefill<false>(g); }
 // The router GEMM: logits = x Wr^T over all T rows, 64 x 128 tiles, K split
 // so that small batches still spread over the GPU.
-__global__ __launch_bounds__(256) void router_gemm(GemmArgs g) { gemm_ring_body<64, 128, 64, 2, 2, false, 3, true>(g); }
+__global__ __launch_bounds__(256) void router_gemm(GemmArgs g) { gemm_ring_dense(g); }
 // The wide tiles never yield (a P workgroup waiting on its CU would only keep
 // D off it), so they leave out the window cells.  They take two weight slots
 // and three activation slots, the activations one slice ahead and their DMA
@@ -817,15 +863,9 @@ __global__ __launch_bounds__(256) void router_gemm(GemmArgs g) { gemm_ring_body<
 // beside the 64-deep form (460 registers) and 1085 us beside a four-stage
 // ring of 32-deep slices (128 KB).  Nothing of D's GEMM1 fits beside GEMM1's
 // tile in either depth (456-460 registers).
-__global__ __launch_bounds__(256) void gemm1_swiglu_wide(GemmArgs g) {
-  gemm_ring_body<256, 256, 64, 2, 2, true, 2, false, 3, false>(g);
-}
-__global__ __launch_bounds__(256) void gemm2_down_wide(GemmArgs g) {
-  gemm_ring_body<256, 256, 64, 2, 2, false, 2, false, 3, false>(g);
-}
-__global__ __launch_bounds__(256) void gemm2_down_wide_share(GemmArgs g) {
-  gemm_ring_body<256, 256, 32, 2, 2, false, 2, false, 3, false>(g);
-}
+__global__ __launch_bounds__(256) void gemm1_swiglu_wide(GemmArgs g) { gemm_ring_wide<true, 64>(g); }
+__global__ __launch_bounds__(256) void gemm2_down_wide(GemmArgs g) { gemm_ring_wide<false, 64>(g); }
+__global__ __launch_bounds__(256) void gemm2_down_wide_share(GemmArgs g) { gemm_ring_wide<false, 32>(g); }
 template <bool ROT, bool STAGE>
 __global__ __launch_bounds__(64 * kDecodeWaves) void gemm1_swiglu_decode(GemmArgs g) {
   gemm_skinny<true, ROT, STAGE>(g);
@@ -837,7 +877,7 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm2_down_decode(GemmArgs 
 
 // ------------------------------------------------------------------ launch
 
-int ffn_bf16_bm(int regime) { return regime == 0 ? 160 : regime == 2 ? 256 : 32; }
+int ffn_bf16_bm(int regime) { return regime == 0 ? kPrefillRows : regime == 2 ? 256 : 32; }
 
 static inline int round8(long long v) { return (int)((v + 7) / 8 * 8); }
 
@@ -872,7 +912,7 @@ hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const vo
   }
   if (regime == 0 || regime == 2) {
     g.n_tiles = gemm == 1 ? (g.N + 127) / 128 : (g.N + 255) / 256;
-    // 160-row tiles (a few m-tiles per expert): the m-tiles of one n-tile
+    // Prefill tiles (a few m-tiles per expert): the m-tiles of one n-tile
     // run together on one XCD and share its weights in that XCD's L2.
     // 256-row tiles (large experts, many m-tiles): tiles are dealt to the
     // XCDs in groups (block_tile), so the whole GPU works through one expert

@@ -353,16 +353,6 @@ constexpr int mx_ring_chunks(int bm, int sa, int sb) {
   return sa * bm * 8 + sb * kMxB * 8 + (sa > 4 ? sa : 4) * (mx_scale_rows(bm) + kMxB) / 4;
 }
 
-// Wait until at most NA min(CA, n) + NB min(CB, n) DMA instructions (and no LDS
-// operation) of this wave are in flight; n is wave-uniform, n >= 0.
-template <int NA, int NB, int CA, int CB, int N = (CA > CB ? CA : CB)>
-__device__ __forceinline__ void wait_rings_lgkm0(int n) {
-  if constexpr (N > 0) {
-    if (n < N) return wait_rings_lgkm0<NA, NB, CA, CB, N - 1>(n);
-  }
-  wait_vmcnt_lgkm0<NA*(CA < N ? CA : N) + NB * (CB < N ? CB : N)>();
-}
-
 template <int BM, int WM, int WN, int SA, int SB, bool GATED, bool SC4>
 __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const TileCoord& tc, u32x4* lds) {
   constexpr int BR = kMxB;
@@ -378,7 +368,7 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
   constexpr int SC_INS = 2;                         // gathers per wave: one of A's rows, one of B's
   constexpr int NA = A_INS + (SC4 ? 0 : SC_INS);    // DMA instructions per wave of an A and a B group
   constexpr int A_CH = BM * CPR, B_CH = BR * CPR;
-  constexpr int NRD = 2 * (FM + FB), NMF = FM * FB;
+  constexpr int NRD = FM + FB, NMF = FM * FB;
   static_assert(WM * WN == 4, "four waves");
   static_assert(A_INS * RPI * 4 == BM && B_INS * RPI * 4 == BR, "slices split into whole DMA instructions");
   static_assert(BR == 4 * 64 && SC_A <= 4 * 64, "one gather of 64 rows per wave");
@@ -450,18 +440,19 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
                                                0);
     }
   };
-  auto issue_a = [&](int kt, int slot) {
-    if constexpr (!SC4) issue_scales(kt, slot);
-#pragma unroll
-    for (int i = 0; i < A_INS; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(&ring_a[slot][(wave * A_INS + i) * 64]), 16,
-                                               a_off[i], kt * BK, 0, 0);
+  // Instruction i of A(kt): the scale gathers first where they go with A.
+  auto issue_a = [&](int i, int kt, int slot) {
+    if (!SC4 && i < SC_INS) {
+      if (i == 0) issue_scales(kt, slot);
+      return;
+    }
+    i -= SC4 ? 0 : SC_INS;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(&ring_a[slot][(wave * A_INS + i) * 64]), 16, a_off[i],
+                                             kt * BK, 0, 0);
   };
-  auto issue_b = [&](int kt, int slot) {
-#pragma unroll
-    for (int i = 0; i < B_INS; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, MOEPD_LPTR(&ring_b[slot][(wave * B_INS + i) * 64]), 16,
-                                               b_off[i & 1], b_row[i] + kt * BK, 0, 0);
+  auto issue_b = [&](int i, int kt, int slot) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, MOEPD_LPTR(&ring_b[slot][(wave * B_INS + i) * 64]), 16,
+                                             b_off[i & 1], b_row[i] + kt * BK, 0, 0);
   };
 
   // step s of a slice: lane half h takes chunks 4s + h and 4s + 2 + h of its
@@ -470,22 +461,17 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
   v8i32 fa[2][FM], fb[2][FB];
   u32x4 sa_raw[FM], sb_raw[FB];
   uint32_t sa[FM], sb[FB];
-  auto read_frags = [&](int aslot, int bslot, int sub, v8i32 (&a)[FM], v8i32 (&b)[FB]) {
-    const u32x4* As = &ring_a[aslot][0];
-    const u32x4* Bs = &ring_b[bslot][0];
+  // Fragment i of step `sub`: A's FM row blocks, then B's FB column blocks
+  // (gate, up).
+  auto read_frag = [&](int i, int aslot, int bslot, int sub, v8i32 (&a)[FM], v8i32 (&b)[FB]) {
     const int c0 = 4 * sub + h, c1 = 4 * sub + 2 + h;
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-      const int r = wm * WTM + fm * 32 + (lane & 31);
-      a[fm] = join(As[r * CPR + (c0 ^ swz<64>(r))], As[r * CPR + (c1 ^ swz<64>(r))]);
+    if (i < FM) {
+      const int r = wm * WTM + i * 32 + (lane & 31);
+      a[i] = join(ring_a[aslot][r * CPR + (c0 ^ swz<64>(r))], ring_a[aslot][r * CPR + (c1 ^ swz<64>(r))]);
+    } else {
+      const int j = i - FM, r = j / FN * BN + wn * WTN + j % FN * 32 + (lane & 31);
+      b[j] = join(ring_b[bslot][r * CPR + (c0 ^ swz<64>(r))], ring_b[bslot][r * CPR + (c1 ^ swz<64>(r))]);
     }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
-        const int r = nb * BN + wn * WTN + fn * 32 + (lane & 31);
-        b[nb * FN + fn] = join(Bs[r * CPR + (c0 ^ swz<64>(r))], Bs[r * CPR + (c1 ^ swz<64>(r))]);
-      }
   };
   // SC4: a row's 16 bytes, the words of four slices.  Otherwise the 16 bytes
   // that hold the row's word among four rows' (4-byte LDS reads right after
@@ -510,21 +496,23 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
   };
 
   f32x16_mx acc[FM][FB];
-  auto mfmas = [&](int sub, const v8i32 (&a)[FM], const v8i32 (&b)[FB]) {
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-      for (int j = 0; j < FB; ++j)
-        acc[fm][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[j], a[fm], acc[fm][j], 0, 0, 0,
-                                                                     (int)(sb[j] >> (16 * sub)), 0,
-                                                                     (int)(sa[fm] >> (16 * sub)));
+  auto mfma = [&](int i, int sub, const v8i32 (&a)[FM], const v8i32 (&b)[FB]) {
+    const int fm = i / FB, j = i % FB;
+    acc[fm][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b[j], a[fm], acc[fm][j], 0, 0, 0,
+                                                                 (int)(sb[j] >> (16 * sub)), 0,
+                                                                 (int)(sa[fm] >> (16 * sub)));
   };
+  auto no_op = [](auto) {};
 
   if constexpr (SC4) issue_scales(0, 0);
 #pragma unroll
   for (int st = 0; st < SB; ++st) {
-    if (st < SA && st < KT) issue_a(st, st);
-    if (st < KT) issue_b(st, st);
+    if (st >= KT) break;
+    if (st < SA)
+#pragma unroll
+      for (int i = 0; i < NA; ++i) issue_a(i, st, st);
+#pragma unroll
+    for (int i = 0; i < B_INS; ++i) issue_b(i, st, st);
   }
 
 #pragma unroll
@@ -536,7 +524,8 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
 
   wait_rings_lgkm0<NA, B_INS, SA - 1, SB - 1>(KT - 1);
   bare_barrier();
-  read_frags(0, 0, 0, fa[0], fb[0]);
+#pragma unroll
+  for (int i = 0; i < FM + FB; ++i) read_frag(i, 0, 0, 0, fa[0], fb[0]);
   read_scales(0);
 
   // One K slice.  LAST: the tile's last slice (no barrier, nothing to read
@@ -549,10 +538,10 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
 #pragma unroll
     for (int j = 0; j < FB; ++j) sb[j] = pick(sb_raw[j], kt);
     // step 0: read step 1's fragments, multiply step 0
-    read_frags(aslot, bslot, 1, fa[1], fb[1]);
-    if constexpr (PEND && !BNOW) issue_b(kt - 1 + SB, bslot == 0 ? SB - 1 : bslot - 1);
-    mfmas(0, fa[0], fb[0]);
-    interleave<0, NMF, PEND && !BNOW ? B_INS : 0, NRD, 0>();
+    weave<NMF, NRD, PEND && !BNOW ? B_INS : 0>([&](auto i) { mfma(i, 0, fa[0], fb[0]); },
+                                               [&](auto i) { read_frag(i, aslot, bslot, 1, fa[1], fb[1]); },
+                                               [&](auto i) { issue_b(i, kt - 1 + SB, bslot == 0 ? SB - 1 : bslot - 1); });
+    auto mul1 = [&](auto i) { mfma(i, 1, fa[1], fb[1]); };
     if constexpr (!LAST) {
       if constexpr (FILL || PEND) wait_vmcnt_lgkm0<NA*(SA - 2) + B_INS * (SB - 2)>();
       else wait_rings_lgkm0<NA, B_INS, SA - 2, SB - 2>(KT - 2 - kt);
@@ -562,16 +551,15 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
         if ((kt & 3) == 0 && kt + 4 < KT) issue_scales(kt + 4, 0);
         if ((kt & 3) == 3) read_scales(0);
       }
-      if constexpr (FILL) {
-        issue_a(kt + SA, aslot);
-        if constexpr (BNOW) issue_b(kt + SB, bslot);
-      }
-      read_frags(na, nb, 0, fa[0], fb[0]);
       if constexpr (!SC4) read_scales(na);
-      mfmas(1, fa[1], fb[1]);
-      interleave<0, NMF, FILL ? NA + (BNOW ? B_INS : 0) : 0, NRD + (SC4 ? 0 : FM + FB), 1>();
+      weave<NMF, NRD, FILL ? NA + (BNOW ? B_INS : 0) : 0>(
+          mul1, [&](auto i) { read_frag(i, na, nb, 0, fa[0], fb[0]); },
+          [&](auto i) {
+            if constexpr (i < NA) issue_a(i, kt + SA, aslot);
+            else issue_b(i - NA, kt + SB, bslot);
+          });
     } else {
-      mfmas(1, fa[1], fb[1]);
+      weave<NMF, 0, 0>(mul1, no_op, no_op);
     }
   };
   int kt = 0, aslot = 0, bslot = 0;

@@ -139,14 +139,14 @@ hipError_t launch_combine(const void* y, const float* topk_w, const int32_t* row
                           void* out, WindowSignal close, hipStream_t s);
 
 // Grouped expert FFN.  `regime` picks the tile configuration (0 = large
-// batches, 160-row tiles; 1 = small batches, 32-row weight-streaming tiles,
+// batches, tiles of up to 192 rows; 1 = small batches, 32-row weight-streaming tiles,
 // one wave of 32 columns each; 2 = very large batches, 256-row tiles);
 // ffn_bf16_bm gives its m-tile height, which the place kernel must use for
 // tile_base.
 int ffn_bf16_bm(int regime);
 // stage (decode regime only): load operands as whole lines through a per-wave
 // LDS stage (faster), or straight into registers with no LDS, so the tiles fit
-// on CUs held by the other phase's 160-row prefill tiles.  share (256-row
+// on CUs held by the other phase's prefill tiles.  share (256-row
 // regime, GEMM2 only): the tiles that leave each CU room for the other
 // phase's staged decode GEMM2 tiles (80 KB of LDS and 364 registers instead
 // of 160 KB and 460; the same bits, 12 % slower alone) run only while the

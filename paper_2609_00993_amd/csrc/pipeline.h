@@ -1,10 +1,12 @@
 // Building blocks of the LDS-ring GEMMs (bf16 and MX FP8): counted waits on
 // this wave's vector-memory operations, the fence-free workgroup barrier,
-// the LDS row swizzle, the instruction-interleaving hints, and the raw
+// the LDS row swizzle, the order of a step's instructions, and the raw
 // buffer-resource word used for bounds-checked DMA.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 namespace moepd {
 
@@ -14,29 +16,6 @@ constexpr int kBufferRsrcWord3 = 0x00020000;
 
 #define MOEPD_GPTR(p) ((const void __attribute__((address_space(1)))*)(p))
 #define MOEPD_LPTR(p) ((void __attribute__((address_space(3)))*)(p))
-
-// s_waitcnt vmcnt(n) with the other counters left alone (gfx9 encoding:
-// vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[5:4] in bits [15:14]).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x70 | 0xF00);
-}
-
-// Wait until at most `newer` slices of NPS DMA instructions each are in
-// flight (newer <= MAXN, wave-uniform).
-template <int NPS, int MAXN>
-__device__ __forceinline__ void wait_slices(int newer) {
-  if constexpr (MAXN > 0) {
-    if (newer >= MAXN) {
-      wait_vmcnt<NPS * MAXN>();
-      return;
-    }
-    wait_slices<NPS, MAXN - 1>(newer);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
 
 // The swizzle depends on the row length.
 // A staged row is BK bf16 = 2 BK bytes = CPR 16-byte chunks, and 256 / (2 BK)
@@ -69,46 +48,54 @@ __device__ __forceinline__ void bare_barrier() {
 }
 
 // s_waitcnt vmcnt(n) lgkmcnt(0): this wave's LDS reads are done and at most
-// n of its vector-memory operations are outstanding.
+// n of its vector-memory operations are outstanding (gfx9 encoding: vmcnt[3:0],
+// expcnt[6:4], lgkmcnt[11:8], vmcnt[5:4] in bits [15:14]).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_lgkm0() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x70);
 }
 
-template <int NPS, int MAXN>
-__device__ __forceinline__ void wait_slices_lgkm0(int newer) {
-  if constexpr (MAXN > 0) {
-    if (newer >= MAXN) {
-      wait_vmcnt_lgkm0<NPS * MAXN>();
-      return;
-    }
-    wait_slices_lgkm0<NPS, MAXN - 1>(newer);
-  } else {
-    wait_vmcnt_lgkm0<0>();
+// Wait until at most NA min(CA, n) + NB min(CB, n) DMA instructions (and no LDS
+// operation) of this wave are in flight; n is wave-uniform, n >= 0.
+template <int NA, int NB, int CA, int CB, int N = (CA > CB ? CA : CB)>
+__device__ __forceinline__ void wait_rings_lgkm0(int n) {
+  if constexpr (N > 0) {
+    if (n < N) return wait_rings_lgkm0<NA, NB, CA, CB, N - 1>(n);
+  }
+  wait_vmcnt_lgkm0<NA*(CA < N ? CA : N) + NB * (CB < N ? CB : N)>();
+}
+
+// f(I), ..., f(N - 1), each index an integral constant.
+template <int I, int N, class F>
+__device__ __forceinline__ void weave_run(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    weave_run<I + 1, N>(f);
   }
 }
 
-// Scheduling-group masks of __builtin_amdgcn_sched_group_barrier.
-constexpr int kSchedMfma = 0x008, kSchedVmem = 0x010, kSchedDsRead = 0x100;
-
-// Ask the scheduler for N MFMAs with NR LDS reads spread over the first half
-// of them (so the reads have the second half to land before the next
-// substep needs them) and NV vector-memory instructions over the second
-// half (sync group SYNC).
-template <int I, int N, int NV, int NR, int SYNC>
-__device__ __forceinline__ void interleave() {
-  if constexpr (I < N) {
-    constexpr int H = (N + 1) / 2;
-    __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, SYNC);
-    if constexpr (I < H) {
-      constexpr int r = NR * (I + 1) / H - NR * I / H;
-      if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(kSchedDsRead, r, SYNC);
-    } else {
-      constexpr int v = NV * (I - H + 1) / (N - H) - NV * (I - H) / (N - H);
-      if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(kSchedVmem, v, SYNC);
-    }
-    interleave<I + 1, N, NV, NR, SYNC>();
+// One step of a ring GEMM: NM MFMAs with NR LDS reads and ND DMA issues
+// placed between them, in exactly this order (a scheduling barrier after each
+// MFMA holds it): the reads go behind the first three quarters of the MFMAs, so
+// they have the rest to land before the next step needs them, and the DMA
+// issues are spread over all of them, so the texture path, which takes a 1 KB
+// instruction in about 16 cycles, never makes a wave wait to issue.  m, r and d
+// take the index of the MFMA, read or issue as an integral constant.  Left to
+// scheduling-group hints the compiler put the slice end's issues before its
+// MFMAs: the 16384-token skewed layer's 256-row GEMMs 4700 / 2545 us with
+// scalar-offset transfers so, 4225 / 2490 as the hints fell with 64-bit
+// addresses, 4070 / 2450 in this order.  Reads over half or a quarter of the
+// MFMAs, and issues over their second half, measured within 1 %.
+template <int NM, int NR, int ND, int I = 0, class M, class R, class D>
+__device__ __forceinline__ void weave(M&& m, R&& r, D&& d) {
+  if constexpr (I < NM) {
+    constexpr int H = (3 * NM + 3) / 4;
+    m(std::integral_constant<int, I>{});
+    if constexpr (I < H) weave_run<NR * I / H, NR*(I + 1) / H>(r);
+    weave_run<ND * I / NM, ND*(I + 1) / NM>(d);
+    __builtin_amdgcn_sched_barrier(0);
+    weave<NM, NR, ND, I + 1>(m, r, d);
   }
 }
 

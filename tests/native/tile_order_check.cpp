@@ -5,7 +5,7 @@
 // rows [offsets[e], offsets[e+1]) without overlap, none longer than the tile
 // height and none empty, for every n-tile.  Shapes: the 256-row tiles dealt
 // to the XCDs in groups (GEMM1 in super-rows of one grid round, GEMM2 in the
-// plain order), the 160-row tiles with the rows shared evenly, and the
+// plain order), the prefill tiles (160 and 192 rows) with the rows shared evenly, and the
 // 32-row decode tiles (striped over the XCDs or in contiguous ranges), over
 // random and skewed row counts and the edges (empty experts, one row, exact
 // multiples of the tile height).
@@ -122,8 +122,9 @@ int main() {
       check_launch(rows, 256, n_tiles, 4, ms, 3, "wide super-rows");
       check_launch(rows, 256, n_tiles, 4, 0, 3, "wide plain");
       check_launch(rows, 256, n_tiles, 8, 5, 3, "wide odd super-rows");
-      // 160-row tiles, consecutive tiles on one XCD, rows shared evenly
+      // 160- and 192-row tiles, consecutive tiles on one XCD, rows shared evenly
       check_launch(rows, 160, n_tiles, 1, 0, 1, "prefill");
+      check_launch(rows, 192, n_tiles, 1, 0, 1, "prefill");
       // 32-row decode tiles: striped when the n-tiles are a multiple of 8
       check_launch(rows, 32, n_tiles, 1, 0, n_tiles % 8 == 0 ? 2 : 1, "decode");
       launches += 5;

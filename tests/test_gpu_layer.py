@@ -111,6 +111,33 @@ def test_layer_parity(name):
         g.close()
 
 
+# Exact rows per expert at the edges of the prefill tiles' heights (32-row
+# blocks, one to three tiles of 192 rows), over K slices from one up: fewer than
+# the rings' slots, as many, and one more; N down to a partial column tile.
+EDGE_ROWS = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 191, 192, 193, 256, 384, 385]
+
+
+@pytest.mark.parametrize("H,I", [(64, 128), (128, 192), (192, 256), (256, 64), (576, 320)])
+def test_prefill_tile_heights(H, I):
+    E, T = len(EDGE_ROWS), sum(EDGE_ROWS)
+    spec = LayerSpec("rows-bf16", E=E, e0=0, E_loc=E, k=1, H=H, I=I, dtype=BF16, T_P=T, T_D=0)
+    inp = make_layer(spec, seed=43)
+    owner = np.random.default_rng(44).permutation(np.repeat(np.arange(E), EDGE_ROWS))
+    inp.logits[0] = np.where(np.arange(E)[None, :] == owner[:, None], 1.0, -1.0).astype(np.float32)
+    g = GpuLayer(inp)
+    try:
+        g.run(0)
+        res = g.fetch(0)
+        ref = oracle.layer(inp.logits[0], inp.x[0], inp.w_gu, inp.w_dn, 1, 0)
+        assert_route_layout_exact(res, ref, "rows-bf16")
+        assert res["counts"].tolist() == EDGE_ROWS
+        # h and y element by element; with k = 1 out is y itself
+        check_h_y(res, ref, inp.w_dn, ref["offsets"], spec, "rows-bf16")
+        assert np.array_equal(res["out"][ref["token_of_row"]], res["y"])
+    finally:
+        g.close()
+
+
 def _snapshot(g, ph):
     res = g.fetch(ph)
     return {k: v.copy() for k, v in res.items() if isinstance(v, np.ndarray)}

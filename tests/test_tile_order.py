@@ -3,7 +3,7 @@
 csrc/tiles.h maps each workgroup id to a logical tile and each logical tile
 to (expert, row range, column block): dealt to the XCDs in groups of 32 for
 the 256-row tiles (GEMM1 in super-rows of one grid round), in contiguous
-ranges with the rows shared evenly for the 160-row tiles, striped over the
+ranges with the rows shared evenly for the prefill tiles, striped over the
 XCDs for the decode tiles.  tests/native/tile_order_check.cpp compiles that
 header for the host and checks, over the library's launch shapes and a
 range of row counts (skewed, ragged, empty experts, exact multiples of the

@@ -3,9 +3,19 @@
 // Same contraction and device-side tile schedule as the bf16 path (see
 // ffn_bf16.hip): GEMM1 h = silu(x_perm W1^T) * (x_perm W3^T) with the SwiGLU
 // in the epilogue, GEMM2 y = h W2^T, rows of expert e = [offsets[e],
-// offsets[e+1]).  Products and sums are float32 FMAs on the vector ALUs; the
-// float32 layer is small (it serves as the exact-arithmetic check of the
-// layer), so a plain 64x64 LDS tile with 4x4 outputs per thread suffices.
+// offsets[e+1]).  Products and sums are float32 (v_mfma_f32_32x32x2_f32: exact
+// products, float32 accumulation).
+//
+// A float32 layer is small (it serves as the exact-arithmetic check of the
+// layer), so what it costs is latency: a workgroup that walks K in steps of a
+// barrier and a memory round trip each took 55 + 66 us for the two GEMMs of 64
+// tokens at H 256, I 512, for 8 MB of operands.  Here a workgroup owns 32 rows
+// x 32 columns (of gate and of up), its four waves take a run of K each, with
+// operands loaded straight into the MFMA lane layout 32 K values at a time and
+// the next 32 in flight, and the four partial sums are added in wave order
+// through LDS: one memory round trip per 128 K values and two barriers in all.
+// 64 tokens 57 + 68 -> 10 + 9 us, 1024 tokens 63 + 95 -> 31 + 20; at H 2048,
+// I 1024 64 tokens 451 + 247 -> 130 + 73, 2048 tokens 1077 + 637 -> 937 + 570.
 #include "common.h"
 #include "kernels.h"
 
@@ -54,75 +64,85 @@ __device__ __forceinline__ bool tile_lookup_f(const GemmArgsF& g, int bm, int bn
   return true;
 }
 
+typedef float f32x16_f __attribute__((ext_vector_type(16)));
+// The caller's weights need no more than a float's alignment.
+typedef float f32x4_f __attribute__((ext_vector_type(4), aligned(4)));
+
 template <bool GATED>
 __global__ __launch_bounds__(256) void gemm_f32(GemmArgsF g) {
-  constexpr int BM = 64, BN = 64, BK = 16;
+  constexpr int BM = 32, BN = 32;
   constexpr int NB = GATED ? 2 : 1;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[NB][BK][BN + 4];
+  __shared__ float part[4][NB][BM][BN + 1];
   int e, m0, m_end, n0;
   if (!tile_lookup_f(g, BM, BN, e, m0, m_end, n0)) return;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 31, kg = lane >> 5;
   const float* Be = g.B + (size_t)e * g.b_stride;
-
-  float acc[NB][4][4];
+  // Block b holds K [32 b, 32 b + 32); of it, lane group kg loads the 16 values
+  // from 32 b + 16 kg on as four vectors, and MFMA (i, j) takes element j of
+  // vector i of both groups (the same K order for A and B).  Rows past the
+  // expert's end repeat its last row (never stored); N is a multiple of 32.
+  const f32x4_f* pa = reinterpret_cast<const f32x4_f*>(g.A + (size_t)min(m0 + r, m_end - 1) * g.K) + kg * 4;
+  const f32x4_f* pb[NB];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
+  for (int n = 0; n < NB; ++n)
+    pb[n] = reinterpret_cast<const f32x4_f*>(Be + (size_t)(n * g.up_row + n0 + r) * g.K) + kg * 4;
+
+  f32x16_f acc[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[n][q] = 0.f;
+  const int KB = g.K / 32, per = (KB + 3) / 4;
+  const int b0 = wave * per, b1 = min(KB, b0 + per);
+  f32x4_f va[2][4], vb[2][NB][4];
+  auto load = [&](int b, f32x4_f (&a)[4], f32x4_f (&w)[NB][4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a[i] = pa[b * 8 + i];
+#pragma unroll
+      for (int n = 0; n < NB; ++n) w[n][i] = pb[n][b * 8 + i];
+    }
+  };
+  auto multiply = [&](const f32x4_f (&a)[4], const f32x4_f (&w)[NB][4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[nb][i][j] = 0.f;
-
-  for (int k0 = 0; k0 < g.K; k0 += BK) {
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int q = tid + i * 256, r = q >> 4, kk = q & 15;
-      const int row = min(m0 + r, m_end - 1);
-      As[kk][r] = g.A[(size_t)row * g.K + k0 + kk];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int brow = nb * g.up_row + min(n0 + r, g.N - 1);
-        Bs[nb][kk][r] = Be[(size_t)brow * g.K + k0 + kk];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], bv[NB][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bv[nb][j] = Bs[nb][kk][tx * 4 + j];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[nb][i][j] = fmaf(a[i], bv[nb][j], acc[nb][i][j]);
-    }
-    __syncthreads();
+        for (int n = 0; n < NB; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][j], w[n][i][j], acc[n], 0, 0, 0);
+  };
+  if (b0 < b1) load(b0, va[0], vb[0]);
+  for (int b = b0; b < b1; b += 2) {
+    if (b + 1 < b1) load(b + 1, va[1], vb[1]);
+    multiply(va[0], vb[0]);
+    if (b + 2 < b1) load(b + 2, va[0], vb[0]);
+    if (b + 1 < b1) multiply(va[1], vb[1]);
   }
+  // accumulator element q of lane (r, kg): row 8 (q / 4) + 4 kg + q % 4, column r
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) part[wave][n][8 * (q >> 2) + 4 * kg + (q & 3)][r] = acc[n][q];
+  __syncthreads();
+  const int col = threadIdx.x & 31;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
+    const int rr = (threadIdx.x >> 5) + 8 * i, row = m0 + rr;
     if (row >= m_end) continue;
+    float v[NB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= g.N) continue;
-      float v = acc[0][i][j];
-      if (GATED) {
-        const float gt = acc[0][i][j];
-        v = gt / (1.f + expf(-gt)) * acc[NB - 1][i][j];
-      }
-      g.C[(size_t)row * g.N + col] = v;
+    for (int n = 0; n < NB; ++n) {
+      v[n] = part[0][n][rr][col];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v[n] += part[w][n][rr][col];
     }
+    if (GATED) v[0] = v[0] / (1.f + expf(-v[0])) * v[NB - 1];
+    g.C[(size_t)row * g.N + n0 + col] = v[0];
   }
 }
 
-int ffn_f32_bm() { return 64; }
+int ffn_f32_bm() { return 32; }
 
 hipError_t launch_ffn_f32(int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn, int e_loc, int H,
                           int I, int max_m_tiles, hipStream_t s) {
@@ -147,7 +167,7 @@ hipError_t launch_ffn_f32(int gemm, const PhaseBuffers& b, const void* w_gu, con
     g.K = I;
     g.up_row = 0;
   }
-  g.n_tiles = (g.N + 63) / 64;
+  g.n_tiles = g.N / 32;
   const long long blocks = ((long long)max_m_tiles * g.n_tiles + 7) / 8 * 8;
   if (gemm == 1)
     gemm_f32<true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);

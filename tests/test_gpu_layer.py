@@ -138,6 +138,24 @@ def test_prefill_tile_heights(H, I):
         g.close()
 
 
+# The float32 tiles: 32-row blocks at their edges; K runs of the four waves
+# that are empty (K = 64), uneven (320) or even, with one block or several.
+@pytest.mark.parametrize("H,I", [(64, 192), (320, 64), (512, 128)])
+def test_f32_tiles(H, I):
+    rows = [1, 31, 32, 33, 64, 65, 0, 130]
+    E, T = len(rows), sum(rows)
+    spec = LayerSpec("rows-f32", E=E, e0=0, E_loc=E, k=1, H=H, I=I, dtype=F32, T_P=T, T_D=0)
+    inp = make_layer(spec, seed=45)
+    owner = np.random.default_rng(46).permutation(np.repeat(np.arange(E), rows))
+    inp.logits[0] = np.where(np.arange(E)[None, :] == owner[:, None], 1.0, -1.0).astype(np.float32)
+    g = GpuLayer(inp)
+    try:
+        g.run(0)
+        assert check_phase(g, inp, 0)["counts"].tolist() == rows
+    finally:
+        g.close()
+
+
 def _snapshot(g, ph):
     res = g.fetch(ph)
     return {k: v.copy() for k, v in res.items() if isinstance(v, np.ndarray)}

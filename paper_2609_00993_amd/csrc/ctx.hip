@@ -12,6 +12,7 @@
 // (Section 5.2); a reset is refused until the phase's enqueued work is done
 // (Section 5.3).
 #include <atomic>
+#include <math.h>
 #include <new>
 #include <string.h>
 
@@ -39,6 +40,7 @@ struct Phase {
   int T = 0;
   int regime = 0;  // tile shape (ffn_bf16_bm / ffn_mx_bm): 0 large batch, 1 small, 2 very large (bf16)
   int bm = 0;
+  bool stage = true;  // form of the small-batch tiles (launch_ffn_bf16)
   int chunk_tokens = 1;
   int nchunks = 1;
   int max_tokens = 0;
@@ -279,7 +281,8 @@ int layout(moe_ctx* ctx, Phase& p, hipStream_t stream) {
     // flop.
     const long long avg = (long long)T * k / c.num_experts;
     p.regime = avg >= 512 ? 2 : avg >= 32 ? 0 : 1;
-    p.bm = ffn_bf16_bm(p.regime);
+    p.stage = ctx->ffn_regime[(&p - ctx->ph) ^ 1].load(std::memory_order_relaxed) != 0;
+    p.bm = ffn_bf16_bm(p.regime, p.stage);
   } else {
     p.regime = 0;
     p.bm = ffn_f32_bm();
@@ -461,11 +464,15 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
     const int max_m_tiles = (int)((rows + p.bm - 1) / p.bm) + c.num_local_experts;
     ctx->ffn_regime[phase].store(p.regime, std::memory_order_relaxed);
     const int other = ctx->ffn_regime[phase ^ 1].load(std::memory_order_relaxed);
-    const bool stage = other != 0;
     // D first (Section 3.1) on one GPU: while D-first admission is on and the
     // context runs D layers, P's 256-row GEMM2 takes the tile that leaves a CU
     // room for D's decode tiles beside it.
     const bool share = phase == MOE_PHASE_P && c.d_priority_us > 0 && other != -1;
+    // m-tiles of a small batch under even routing: the experts it touches, one
+    // standard deviation above the mean (a few tiles more than one round holds
+    // cost a second one)
+    const double miss = pow(1.0 - (double)c.top_k / c.num_experts, (double)p.T), loc = c.num_local_experts;
+    const double m_tiles_hint = fmin(loc, loc * (1.0 - miss) + sqrt(loc * miss * (1.0 - miss)));
     for (int gemm = 1; gemm <= 2; ++gemm) {
       st = timed(p, gemm == 1 ? MOE_KERNEL_GEMM1 : MOE_KERNEL_GEMM2, stream, [&] {
         if (c.dtype == MOE_DTYPE_FP8)
@@ -474,7 +481,7 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
                                c.num_local_experts, c.hidden, c.inter, max_m_tiles, yield_of(ctx, phase), stream);
         if (c.dtype == MOE_DTYPE_BF16)
           return launch_ffn_bf16(p.regime, gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden,
-                                 c.inter, max_m_tiles, stage, share, yield_of(ctx, phase),
+                                 c.inter, max_m_tiles, m_tiles_hint, p.stage, share, yield_of(ctx, phase),
                                  ctx->ph[phase ^ 1].b.signal, stream);
         return launch_ffn_f32(gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden, c.inter,
                               max_m_tiles, stream);

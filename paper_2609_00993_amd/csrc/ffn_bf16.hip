@@ -32,12 +32,14 @@
 //    expert's rows are shared evenly among its ceil(rows / 192) m-tiles, each
 //    of which streams the expert's weights once more;
 //  * small batches (decode, a few rows per expert): the layer is a weight
-//    stream, one 32-row m-tile and 32 columns per single-wave workgroup,
-//    two 64-deep K blocks in flight.  Each block is loaded with whole-line
-//    reads and transposed through the wave's own 12 KB LDS stage into MFMA
-//    operand layout; beside the other phase's prefill tiles (which
-//    leave 4 KB of LDS) the tile loads straight into operand registers
-//    instead, with no LDS, so it can share their CUs.
+//    stream, up to 96 rows and 32 or 64 columns per single-wave workgroup,
+//    cut to the 32-row blocks it holds.  64-deep K blocks come by whole-line
+//    DMA into the wave's own LDS ring, two to four in flight; beside the other
+//    phase's prefill tiles (which leave 3 KB of LDS) a 32-row tile loads
+//    straight into operand registers instead, with no LDS, so it can share
+//    their CUs.
+#include <math.h>
+
 #include <type_traits>
 
 #include "common.h"
@@ -106,109 +108,128 @@ __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 
 // 1.5 tiles per CU left half the CUs with two, which then set the pace).
 constexpr int kDecodeWaves = 1;
 
-template <bool GATED, bool ROT>
-__device__ __forceinline__ void gemm_skinny_tile(const GemmArgs& g, const TileCoord& tc) {
-  static_assert(kDecodeWaves == 1, "the LDS stage below is private to the workgroup's one wave");
-  constexpr int BN = 32 * kDecodeWaves;
-  constexpr int NB = GATED ? 2 : 1;
-  constexpr int NP = 1 + NB;  // panels: the tile's activation rows, then its weight rows (gate, up)
-  // A 64-deep K block of one panel is 32 rows x 128 B.  It is loaded as four
-  // 1 KB instructions that each read eight whole 128-byte row pieces (lane
-  // l: row 8i + l/8, 16-byte chunk l%8): reading 16 bytes from each of 32
-  // rows per instruction, as the MFMA lane layout would, reaches only about a
-  // quarter of the per-CU rate of whole-line reads.  The block then goes
-  // through this wave's LDS stage, chunk c of row r at slot
-  // 8r + (c ^ stage_swz(r)) (no bank conflicts on either side), and is read
-  // back in the MFMA layout.
-  __shared__ u32x4 stage[NP][32 * 8];
+// A staged tile of up to 32 MB rows of one expert and NB blocks of 32 weight
+// rows (gate and up, or columns of y).  A K block of a panel (32 rows, 64 deep)
+// is 4 KB, moved HBM -> LDS by four 1 KB DMA instructions that each read eight
+// whole 128-byte row pieces (lane l: row 8i + l/8, 16-byte chunk l%8): reading
+// 16 bytes from each of 32 rows per instruction, as the MFMA lane layout would,
+// reaches only about a quarter of the per-CU rate of whole-line reads.  Chunk
+// c of row r comes to slot 8r + (c ^ stage_swz(r)) (no bank conflicts when the
+// fragments are read in the MFMA layout).  SLOTS blocks are in the wave's ring;
+// a block's slot is refilled as soon as its fragments are in registers, so no
+// barrier is needed and what is in flight takes no registers.
+//
+// Taller tiles where an expert has the rows: all its 32-row blocks then use
+// one pass over the weights.  With one tile per 32 rows, a skewed batch's
+// popular experts streamed their weights from L2 once per block: 256 tokens
+// at Zipf(1.2), H 7168, I 2048 took 444 + 252 us for the two GEMMs, 330 + 167
+// with even routing; now 414 + 228 and 327 + 162 (the weights alone are 313 +
+// 157 at a copy's rate).
+template <int MB, int NB, int SLOTS, bool GATED, bool ROT>
+__device__ __forceinline__ void gemm_skinny_tile(const GemmArgs& g, const TileCoord& tc, u32x4* lds) {
+  static_assert(kDecodeWaves == 1, "the LDS ring below is private to the workgroup's one wave");
+  constexpr int NP = MB + NB;  // 32-row panels: the tile's activation rows, then its weight rows
+  constexpr int PANEL = 32 * 8;  // 16-byte chunks of a panel's 64-deep K block
   const int lane = threadIdx.x & 63;
-  const int lr = lane >> 3, lc = lane & 7;  // coalesced side: row within eight, chunk
+  const int lr = lane >> 3, lc = lane & 7;  // DMA side: row within eight, chunk
   const int r = lane & 31, kg = lane >> 5;  // MFMA side
-  const int col = tc.n0 + r;
-  const uint16_t* Be = g.B + (size_t)tc.e * g.b_stride;
-  const u32x4* base[NP];
-  base[0] = reinterpret_cast<const u32x4*>(g.A);
-  base[1] = reinterpret_cast<const u32x4*>(Be);
-  if (GATED) base[NP - 1] = reinterpret_cast<const u32x4*>(Be + (size_t)g.up_row * g.K);
-  const int kv = g.K / 8;  // 16-byte chunks per row
-  // Chunk offset of this lane's row piece in block 0.  32 bits suffice: the
-  // decode regime holds fewer than 32 rows per expert on average, so under
-  // 32 x 1024 rows of at most 2048 chunks, and weight panels hold at most
-  // 2 x 16384 rows.
-  int off[NP][4];
+  const int m0 = __builtin_amdgcn_readfirstlane(tc.m0), m_end = __builtin_amdgcn_readfirstlane(tc.m_end);
+  const int n0 = __builtin_amdgcn_readfirstlane(tc.n0);
+  const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(g.A + (size_t)m0 * g.K), (short)0, min(m_end - m0, 32 * MB) * g.K * 2, kBufferRsrcWord3);
+  const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(g.B + (size_t)__builtin_amdgcn_readfirstlane(tc.e) * g.b_stride), (short)0,
+      (GATED ? g.up_row + g.N : g.N) * g.K * 2, kBufferRsrcWord3);
+  // Instruction i of a panel reads rows 8i .. 8i + 7, eight lanes to a row's
+  // 128 bytes; stage_swz repeats every 16 rows, so i and i + 2 share the lane's
+  // offset within 16 rows.
+  int off[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int rr = 8 * i + lr;
-    off[0][i] = min(tc.m0 + rr, tc.m_end - 1) * kv + lc;
-    const int cc = min(tc.n0 + rr, g.N - 1) * kv + lc;
+  for (int i = 0; i < 2; ++i) off[i] = ((8 * i + lr) * g.K + (lc ^ stage_swz(8 * i + lr)) * 8) * 2;
+  const int row16 = 16 * g.K * 2;  // bytes
+  const int KB = g.K / 64;
+  const int krot = ROT ? k_rotation(tc, g.n_tiles, GATED ? 32 : 32 * NB, KB) : 0;
+  auto issue = [&](int kb, int slot) {
+    if (ROT) {
+      kb += krot;
+      if (kb >= KB) kb -= KB;
+    }
+    const int k = kb * 128;
+    u32x4* dst = lds + slot * (NP * PANEL);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) off[1 + j][i] = cc;
-  }
-  int wslot[4];  // LDS slot of this lane's chunk for each of the four instructions
+    for (int p = 0; p < MB; ++p)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) wslot[i] = (8 * i + lr) * 8 + (lc ^ stage_swz(8 * i + lr));
+      for (int i = 0; i < 4; ++i)
+        // rows past the expert's end lie past the resource: the row part stays in the lane offset, which is checked
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(dst + p * PANEL + i * 64), 16,
+                                                 off[i & 1] + (2 * p + (i >> 1)) * row16, k, 0, 0);
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, MOEPD_LPTR(dst + (MB + p) * PANEL + i * 64), 16, off[i & 1],
+                                                 k + (p * (GATED ? g.up_row : 32) + n0) * g.K * 2 + (i >> 1) * row16, 0, 0);
+  };
   // lane group kg holds k in [64*kb + 32*kg, +32) as four 16-byte chunks;
   // MFMA step s takes chunk s of both groups (the same k map for A and B).
   int rslot[4];
 #pragma unroll
   for (int st = 0; st < 4; ++st) rslot[st] = r * 8 + ((4 * kg + st) ^ stage_swz(r));
 
-  f32x16_t acc[NB];
+  f32x16_t acc[MB][NB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[m][j][q] = 0.f;
 
-  const int KB = g.K / 64;
-  const int krot = ROT ? k_rotation(tc, g.n_tiles, BN, KB) : 0;
-  constexpr int PF = 2;  // 64-deep K blocks in flight per wave (a static register ring)
-  u32x4 v[PF][NP][4];
-  auto load = [&](int kb, u32x4 (&d)[NP][4]) {
-    if (ROT) {
-      kb += krot;
-      if (kb >= KB) kb -= KB;
-    }
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
+  for (int q = 0; q < SLOTS; ++q)
+    if (q < KB) issue(q, q);
+  int slot = 0;
+  for (int kb = 0; kb < KB; ++kb) {
+    // block kb has landed once at most the newer blocks remain
+    wait_rings_lgkm0<4 * NP, 0, SLOTS - 1, 0>(KB - 1 - kb);
+    const u32x4* src = lds + slot * (NP * PANEL);
+    u32x4 f[4][NP];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) d[p][i] = base[p][off[p][i] + kb * 8];
-  };
+    for (int st = 0; st < 4; ++st)
 #pragma unroll
-  for (int q = 0; q < PF; ++q)
-    if (q < KB) load(q, v[q]);
-  for (int kb0 = 0; kb0 < KB; kb0 += PF) {
+      for (int p = 0; p < NP; ++p) f[st][p] = src[p * PANEL + rslot[st]];
+    wait_vmcnt_lgkm0<63>();  // the block is in registers: its slot is free
+    if (kb + SLOTS < KB) issue(kb + SLOTS, slot);
 #pragma unroll
-    for (int q = 0; q < PF; ++q) {
-      const int kb = kb0 + q;
-      if (kb < KB) {
-        // LDS operations of one wave run in order, so these writes land after
-        // the previous block's reads and before this block's.
+    for (int st = 0; st < 4; ++st)
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
+      for (int m = 0; m < MB; ++m)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) stage[p][wslot[i]] = v[q][p][i];
-        if (kb + PF < KB) load(kb + PF, v[q]);
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-          const u32x4 a = stage[0][rslot[st]];
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(stage[1 + j][rslot[st]]), acc[j],
-                                                            0, 0, 0);
-        }
-      }
-    }
+        for (int j = 0; j < NB; ++j)
+          acc[m][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(f[st][MB + j]), as_bf16x8(f[st][m]), acc[m][j],
+                                                              0, 0, 0);
+    if (++slot == SLOTS) slot = 0;
   }
 
-  if (col < g.N) {
+  // the weight fragment goes first, so lane (r, kg) holds row r of each block
+  // and its columns 8q + 4 kg .. + 3
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int row = tc.m0 + acc_row(q, lane);
-      if (row < tc.m_end) {
-        if (GATED)
-          static_cast<uint16_t*>(g.C)[(size_t)row * g.N + col] = f32_to_bf16(silu_mul(acc[0][q], acc[NB - 1][q]));
-        else
-          static_cast<float*>(g.C)[(size_t)row * g.N + col] = acc[0][q];
+  for (int m = 0; m < MB; ++m) {
+    const int row = m0 + 32 * m + r;
+    if (row >= m_end) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const size_t at = (size_t)row * g.N + n0 + 8 * q + 4 * kg;
+      if (GATED) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16(silu_mul(acc[m][0][4 * q + i], acc[m][NB - 1][4 * q + i]));
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.C) + at) = u32x2{w[0] | w[1] << 16, w[2] | w[3] << 16};
+      } else {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + at + 32 * j) =
+              f32x4{acc[m][j][4 * q], acc[m][j][4 * q + 1], acc[m][j][4 * q + 2], acc[m][j][4 * q + 3]};
       }
     }
   }
@@ -289,16 +310,37 @@ __device__ __forceinline__ void gemm_skinny_tile_direct(const GemmArgs& g, const
   }
 }
 
-template <bool GATED, bool ROT, bool STAGE>
+// Staged decode tiles hold up to kDecodeRows rows, cut to their 32-row blocks:
+// 96 is what one slot of the eight-per-CU form takes.
+constexpr int kDecodeRows = 96;
+constexpr int decode_chunks(int per_cu) { return 160 / per_cu / 4 * 256; }  // 16-byte chunks of LDS: whole panels
+constexpr int decode_slots(int mb, int nb, int per_cu) {
+  const int n = decode_chunks(per_cu) / ((mb + nb) * 32 * 8);
+  return n > 4 ? 4 : n;
+}
+// 32-column blocks of a staged GEMM2 tile: two, which halves the activation
+// reads (256 tokens at Zipf(1.2), H 2560, I 768: 57 us against 64); one where
+// the weight rows start on the same memory channel (ROT; even 128 tokens at H
+// 7168, I 2048: 161 us against 167).
+constexpr int gemm2_blocks(bool rot) { return rot ? 1 : 2; }
+template <bool GATED, bool ROT, int PER_CU>
 __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
-  constexpr int BM = 32, BN = 32 * kDecodeWaves;
   const int L = block_tile(g);
   if (L < 0) return;
   yield_to_window(g.yield);
   TileCoord tc;
-  tile_at(g, L, BM, BN, tc);
-  if constexpr (STAGE) gemm_skinny_tile<GATED, ROT>(g, tc);
-  else gemm_skinny_tile_direct<GATED, ROT>(g, tc);
+  if constexpr (PER_CU > 0) {
+    constexpr int NB = GATED ? 2 : gemm2_blocks(ROT);
+    tile_at(g, L, kDecodeRows, GATED ? 32 : 32 * NB, tc);
+    __shared__ u32x4 lds[decode_chunks(PER_CU)];
+    const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
+    if (blocks <= 1) gemm_skinny_tile<1, NB, decode_slots(1, NB, PER_CU), GATED, ROT>(g, tc, lds);
+    else if (blocks == 2) gemm_skinny_tile<2, NB, decode_slots(2, NB, PER_CU), GATED, ROT>(g, tc, lds);
+    else gemm_skinny_tile<3, NB, decode_slots(3, NB, PER_CU), GATED, ROT>(g, tc, lds);
+  } else {
+    tile_at(g, L, 32, 32 * kDecodeWaves, tc);
+    gemm_skinny_tile_direct<GATED, ROT>(g, tc);
+  }
 }
 
 // One workgroup of 4 waves computes a BM x BN output tile of one expert.
@@ -866,18 +908,20 @@ __global__ __launch_bounds__(256) void router_gemm(GemmArgs g) { gemm_ring_dense
 __global__ __launch_bounds__(256) void gemm1_swiglu_wide(GemmArgs g) { gemm_ring_wide<true, 64>(g); }
 __global__ __launch_bounds__(256) void gemm2_down_wide(GemmArgs g) { gemm_ring_wide<false, 64>(g); }
 __global__ __launch_bounds__(256) void gemm2_down_wide_share(GemmArgs g) { gemm_ring_wide<false, 32>(g); }
-template <bool ROT, bool STAGE>
+template <bool ROT, int PER_CU>
 __global__ __launch_bounds__(64 * kDecodeWaves) void gemm1_swiglu_decode(GemmArgs g) {
-  gemm_skinny<true, ROT, STAGE>(g);
+  gemm_skinny<true, ROT, PER_CU>(g);
 }
-template <bool ROT, bool STAGE>
+template <bool ROT, int PER_CU>
 __global__ __launch_bounds__(64 * kDecodeWaves) void gemm2_down_decode(GemmArgs g) {
-  gemm_skinny<false, ROT, STAGE>(g);
+  gemm_skinny<false, ROT, PER_CU>(g);
 }
 
 // ------------------------------------------------------------------ launch
 
-int ffn_bf16_bm(int regime) { return regime == 0 ? kPrefillRows : regime == 2 ? 256 : 32; }
+int ffn_bf16_bm(int regime, bool stage) {
+  return regime == 0 ? kPrefillRows : regime == 2 ? 256 : stage ? kDecodeRows : 32;
+}
 
 static inline int round8(long long v) { return (int)((v + 7) / 8 * 8); }
 
@@ -886,8 +930,8 @@ long long ffn_bf16_handover_words(long long rows_cap, int e_loc, int H) {
 }
 
 hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn,
-                           int e_loc, int H, int I, int max_m_tiles, bool stage, bool share, YieldTo yield,
-                           const int32_t* other_window, hipStream_t s) {
+                           int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool stage, bool share,
+                           YieldTo yield, const int32_t* other_window, hipStream_t s) {
   GemmArgs g{};
   g.yield = yield;
   g.offsets = b.offsets;
@@ -957,21 +1001,33 @@ hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const vo
       }
     }
   } else {
-    constexpr int bn = 32 * kDecodeWaves, threads = 64 * kDecodeWaves;
-    g.n_tiles = (g.N + bn - 1) / bn;
+    const bool rot = g.K % 2048 == 0;
+    g.n_tiles = g.N / (stage && gemm == 2 ? 32 * gemm2_blocks(rot) : 32);
     g.n_group = 1;
     g.m_super = 0;
     g.xcd_local = g.n_tiles % 8 == 0 ? 2 : 1;
     const dim3 grid(round8((long long)max_m_tiles * g.n_tiles));
-    const bool rot = g.K % 2048 == 0;
-    auto go = [&](auto k) { k<<<grid, threads, 0, s>>>(g); };
-    if (gemm == 1) {
-      if (stage) rot ? go(gemm1_swiglu_decode<true, true>) : go(gemm1_swiglu_decode<false, true>);
-      else rot ? go(gemm1_swiglu_decode<true, false>) : go(gemm1_swiglu_decode<false, false>);
-    } else {
-      if (stage) rot ? go(gemm2_down_decode<true, true>) : go(gemm2_down_decode<false, true>);
-      else rot ? go(gemm2_down_decode<true, false>) : go(gemm2_down_decode<false, false>);
-    }
+    auto go = [&](auto k) { k<<<grid, 64 * kDecodeWaves, 0, s>>>(g); };
+    auto form = [&](auto per_cu) {
+      constexpr int P = decltype(per_cu)::value;
+      if (gemm == 1) rot ? go(gemm1_swiglu_decode<true, P>) : go(gemm1_swiglu_decode<false, P>);
+      else rot ? go(gemm2_down_decode<true, P>) : go(gemm2_down_decode<false, P>);
+    };
+    // Workgroups per CU.  Four (three slots of a 32-row tile) while they hold
+    // all the expected tiles, so that few waves keep enough in flight (256 GEMM1
+    // tiles 46 us, 89 with eight), or while their last round is nearly full (skewed
+    // 2048 GEMM1 tiles 391 us, 414 with eight; beside the other phase's tiles,
+    // where few waves fit, D's layer 847 / 909 us).  Else eight with one slot (the
+    // block being multiplied is in registers meanwhile) while these run at once
+    // (1470 GEMM1 tiles 225 us, 252 with four; 0.15 of a round passes unnoticed),
+    // or six if its last round is the fuller (2560 GEMM2 tiles 51 / 58 us).
+    const double tiles = m_tiles_hint * g.n_tiles;
+    auto rounds = [&](int per_cu) { return tiles / (256.0 * per_cu); };
+    auto cost = [&](int per_cu) { return ceil(rounds(per_cu) - 0.15) / rounds(per_cu); };
+    if (!stage) form(std::integral_constant<int, 0>{});
+    else if (tiles <= 4 * 256 || cost(4) <= 1.1) form(std::integral_constant<int, 4>{});
+    else if (rounds(8) > 1.15 && cost(6) < cost(8)) form(std::integral_constant<int, 6>{});
+    else form(std::integral_constant<int, 8>{});
   }
   return hipGetLastError();
 }

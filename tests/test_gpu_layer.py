@@ -138,6 +138,31 @@ def test_prefill_tile_heights(H, I):
         g.close()
 
 
+# The staged decode tiles: 32-row blocks and one to three tiles of 96 rows at
+# their edges, K blocks fewer and more than the ring's slots, rotated K (rows of
+# a multiple of 4 KB) or not, and tile counts that choose four, eight (16 experts
+# x 80 or 128 column tiles) and six (16 x 160) workgroups per CU.
+@pytest.mark.parametrize("H,I", [(64, 64), (192, 320), (128, 2560), (2048, 128), (4096, 64), (64, 4096), (128, 5120)])
+def test_decode_tile_heights(H, I):
+    rows = [1, 31, 32, 33, 64, 65, 95, 96, 97, 128, 192, 193, 0, 2, 3, 40]
+    E, E_loc, T = 64, len(rows), sum(rows)
+    spec = LayerSpec("rows-decode", E=E, e0=8, E_loc=E_loc, k=1, H=H, I=I, dtype=BF16, T_P=0, T_D=T)
+    inp = make_layer(spec, seed=47)
+    owner = 8 + np.random.default_rng(48).permutation(np.repeat(np.arange(E_loc), rows))
+    inp.logits[1] = np.where(np.arange(E)[None, :] == owner[:, None], 1.0, -1.0).astype(np.float32)
+    g = GpuLayer(inp)
+    try:
+        g.run(1)
+        res = g.fetch(1)
+        ref = oracle.layer(inp.logits[1], inp.x[1], inp.w_gu, inp.w_dn, 1, 8)
+        assert_route_layout_exact(res, ref, "rows-decode")
+        assert res["counts"].tolist() == rows
+        check_h_y(res, ref, inp.w_dn, ref["offsets"], spec, "rows-decode")
+        assert np.array_equal(res["out"][ref["token_of_row"]], res["y"])
+    finally:
+        g.close()
+
+
 # The float32 tiles: 32-row blocks at their edges; K runs of the four waves
 # that are empty (K = 64), uneven (320) or even, with one block or several.
 @pytest.mark.parametrize("H,I", [(64, 192), (320, 64), (512, 128)])

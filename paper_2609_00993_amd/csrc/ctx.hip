@@ -276,7 +276,7 @@ int layout(moe_ctx* ctx, Phase& p, hipStream_t stream) {
     p.bm = ffn_mx_bm(p.regime, avg);
   } else if (c.dtype == MOE_DTYPE_BF16) {
     // Rows per resident expert expected under even routing: T*k/E.  Small
-    // batches stream weights (32-row tiles); large ones take tiles of up to 192
+    // batches stream weights (32-row tiles); large ones take tiles of up to 160
     // rows, and very large ones 256-row tiles, which move fewer bytes into LDS per
     // flop.
     const long long avg = (long long)T * k / c.num_experts;
@@ -473,15 +473,21 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
     // cost a second one)
     const double miss = pow(1.0 - (double)c.top_k / c.num_experts, (double)p.T), loc = c.num_local_experts;
     const double m_tiles_hint = fmin(loc, loc * (1.0 - miss) + sqrt(loc * miss * (1.0 - miss)));
+    // Small tiles of both phases at once: P's leave the CUs LDS for the kernels of
+    // a D layer they wait for, and D's fit where one of P's has ended.
+    const bool beside = p.regime == 1 && (share || (phase == MOE_PHASE_D && other == 1));
     for (int gemm = 1; gemm <= 2; ++gemm) {
       st = timed(p, gemm == 1 ? MOE_KERNEL_GEMM1 : MOE_KERNEL_GEMM2, stream, [&] {
         if (c.dtype == MOE_DTYPE_FP8)
           return launch_ffn_mx(p.regime, gemm, p.b, mx_of(ctx, p),
                                MxWeights{ctx->w.w_gate_up, ctx->w.w_gate_up_scales, ctx->w.w_down, ctx->w.w_down_scales},
-                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, yield_of(ctx, phase), stream);
+                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, m_tiles_hint,
+                               beside && phase == MOE_PHASE_P,
+                               yield_of(ctx, phase), stream);
         if (c.dtype == MOE_DTYPE_BF16)
           return launch_ffn_bf16(p.regime, gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden,
-                                 c.inter, max_m_tiles, m_tiles_hint, p.stage, share, yield_of(ctx, phase),
+                                 c.inter, max_m_tiles, m_tiles_hint, p.stage, share,
+                                 beside ? (phase == MOE_PHASE_P ? 6 : 8) : 0, yield_of(ctx, phase),
                                  ctx->ph[phase ^ 1].b.signal, stream);
         return launch_ffn_f32(gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden, c.inter,
                               max_m_tiles, stream);

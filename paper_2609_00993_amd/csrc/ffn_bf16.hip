@@ -23,13 +23,13 @@
 //    one slice ahead; GEMM2 also has a share form in 32-deep slices that
 //    leaves a CU room for the other phase's decode tiles (gemm_ring_body and
 //    the kernels below);
-//  * large batches (prefill): 256 threads, tiles of up to 192 rows x (128 gate
+//  * large batches (prefill): 256 threads, tiles of up to 160 rows x (128 gate
 //    + 128 up) or 256 columns, cut to the 32-row blocks they hold, 32x32x16
-//    MFMAs; up to 160 rows the four waves stand side by side along N.
+//    MFMAs, the four waves side by side along N.
 //    Operands stream HBM -> LDS by 16-byte DMA into rings of 64-deep K slices
 //    (157 KB); fragments are double-buffered in registers and the LDS reads
 //    and DMA issues are placed between the MFMAs (see gemm_ring_body).  An
-//    expert's rows are shared evenly among its ceil(rows / 192) m-tiles, each
+//    expert's rows are shared evenly among its ceil(rows / 160) m-tiles, each
 //    of which streams the expert's weights once more;
 //  * small batches (decode, a few rows per expert): the layer is a weight
 //    stream, up to 96 rows and 32 or 64 columns per single-wave workgroup,
@@ -406,8 +406,7 @@ constexpr int kCachePolicyAgent = 0x10;  // sc1: coherent at agent scope
 // followed, over the next slice's substeps, by A(j + 1), so the counted wait
 // at a slice end retires the next slice's weights while that slice's
 // activations, issued a slice earlier, have had up to two slices' time to
-// land.  With SA = STAGES - 1 it is the weights that run ahead: A(j) goes out
-// whole at the slice end, then B(j + 1) over the next slice's substeps.  WIN:
+// land.  WIN:
 // the tile keeps the LDS cells of the D window word (tiles that never yield
 // leave them out, which frees the LDS for the third activation slot).
 //
@@ -438,7 +437,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
   static_assert(FM * 32 == WTM && FN * 32 == WTN, "wave tile must be a multiple of 32x32");
   static_assert(STAGES >= 2 && NPS * (STAGES - 1) < 64, "pipeline depth");
   constexpr int LEAD = SA - STAGES;  // slices the activations run ahead of the weights
-  static_assert(LEAD == 0 || (LEAD == 1 && STAGES == 2 && !WIN && !DENSE) || (LEAD == -1 && SA >= 2),
+  static_assert(LEAD == 0 || (LEAD == 1 && STAGES == 2 && !WIN && !DENSE),
                 "activation lead: two weight slots only");
   // The DMA group a slice end would issue goes out in parts, so the
   // vector-memory queue takes a part at a time beside the MFMAs instead of
@@ -447,10 +446,9 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
   // of the next slice (into the slot the barrier freed).  With it the
   // weights (one slice to land) go out whole at the slice end and the
   // activations' A_INS make SUB - 1 parts, one per substep of the next slice
-  // but its last (their slot too was freed a barrier earlier).  With the
-  // weights ahead it is the other way round.
-  constexpr int PART_N = LEAD == 1 ? A_INS : LEAD == -1 ? B_INS : NPS;  // instructions cut into parts
-  constexpr int NPART = LEAD != 0 ? SUB - 1 : SUB;                      // parts
+  // but its last (their slot too was freed a barrier earlier). 
+  constexpr int PART_N = LEAD == 1 ? A_INS : NPS;  // instructions cut into parts
+  constexpr int NPART = LEAD == 1 ? SUB - 1 : SUB;      // parts
   constexpr int END_PARTS = NPART - (SUB - 1);         // parts issued at the slice end (0 or 1)
   constexpr int PART0 = END_PARTS * PART_N / NPART;     // instructions among them
   static_assert(2 * A_INS + B_INS < 64, "prologue wait range");
@@ -524,11 +522,10 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
     for (int i = 0; i < B_INS; ++i) issue_b1(i, kt * BK, slot);
   };
   // Instruction i of slice kt's spread DMA into slot `slot`: of A's A_INS then
-  // B's B_INS, or with a lead of the leading operand's alone.  Part p of it is
+  // B's B_INS, or with the lead of A's alone.  Part p of it is
   // [PART_N p / NPART, PART_N (p + 1) / NPART).
   auto issue_part1 = [&](int i, int kt, int slot) {
-    if (LEAD == -1) issue_b1(i, kt * BK, slot);
-    else if (LEAD == 1 || i < A_INS) issue_a1(i, kt * BK, slot);
+    if (LEAD == 1 || i < A_INS) issue_a1(i, kt * BK, slot);
     else issue_b1(i - A_INS, kt * BK, slot);
   };
   auto load_window = [&] {
@@ -563,13 +560,13 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
 
   if constexpr (DENSE) KT = min(g.dense_ks, KT - tc.split * g.dense_ks);
   // The prologue's groups go out whole, in the order of the K loop's queue:
-  // without a lead, or with the weights ahead, A(j) then B(j); with the
-  // activation lead B(j) then A(j + 1).
+  // without a lead A(j) then B(j); with the activation lead B(j) then
+  // A(j + 1).
   if constexpr (LEAD == 1) issue_a(0, 0);
 #pragma unroll
   for (int st = 0; st < STAGES; ++st) {
     if (st >= KT) break;
-    if (LEAD <= 0 && st < SA) issue_a(st, st);
+    if (LEAD == 0) issue_a(st, st);
     issue_b(st, st);
     if (LEAD == 1 && st + 1 < KT) issue_a(st + 1, st + 1);
   }
@@ -584,9 +581,8 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
 
   // Slice 0 has landed once at most min(STAGES - 1, KT - 1) newer slices
   // remain; with the activation lead, once at most A(1), B(1) and A(2) (those
-  // the tile has) remain behind B(0); with the weights ahead, once at most the
-  // newer slices of either ring remain.
-  if constexpr (LEAD <= 0) {
+  // the tile has) remain behind B(0).
+  if constexpr (LEAD == 0) {
     wait_rings_lgkm0<A_INS, B_INS, SA - 1, STAGES - 1>(KT - 1);
   } else {
     if (KT > 2) wait_vmcnt_lgkm0<2 * A_INS + B_INS>();
@@ -612,7 +608,7 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
     if constexpr (LEAD == 1) {
       pkt = kt + 2;
       pslot = aslot + 2 >= SA ? aslot + 2 - SA : aslot + 2;
-    } else {  // also the slice and slot of B with the weights ahead
+    } else {
       pkt = kt - 1 + STAGES;
       pslot = bslot == 0 ? STAGES - 1 : bslot - 1;
     }
@@ -661,10 +657,9 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
           }
         }
         auto rd = [&](auto i) { read_frag(i, na, nb, 0, fa[nxt], fb[nxt]); };
-        constexpr int ND = MODE != 0 ? 0 : LEAD == 1 ? B_INS : LEAD == -1 ? A_INS : PART0;
+        constexpr int ND = MODE != 0 ? 0 : LEAD == 1 ? B_INS : PART0;
         weave<NMF, NRD, ND>(mul, rd, [&](auto i) {
           if constexpr (LEAD == 1) issue_b1(i, (kt + STAGES) * BK, bslot);
-          else if constexpr (LEAD == -1) issue_a1(i, (kt + SA) * BK, aslot);
           else issue_part1(i, kt + STAGES, bslot);
         });
       } else {
@@ -681,12 +676,11 @@ __device__ __forceinline__ void gemm_ring_body(const GemmArgs& g, const TileCoor
   using M1 = std::integral_constant<int, 1>;
   using NoPend = std::false_type;
   using Pend = std::true_type;
-  constexpr int REFILL = LEAD == -1 ? SA : STAGES;  // a slice end refills for slice kt + REFILL
-  if (KT > REFILL) {
+  if (KT > STAGES) {
     // the prologue issued its groups whole: nothing pending in slice 0
     slice(M0{}, NoPend{}, kt, aslot, bslot);
     advance();
-    for (++kt; kt < KT - REFILL; ++kt) {
+    for (++kt; kt < KT - STAGES; ++kt) {
       slice(M0{}, Pend{}, kt, aslot, bslot);
       advance();
     }
@@ -851,18 +845,17 @@ __device__ __forceinline__ void gemm_ring_wide(const GemmArgs& g) {
   }
 }
 
-// Prefill tiles of up to 192 rows, cut to the 32-row blocks they hold: the
-// MFMAs, A transfers and fragment reads go with a tile's rows.  Six blocks take
-// a 2 x 2 grid of waves, whose fragment reads per MFMA are fewer, and two
-// activation slots, which is what the LDS leaves beside three weight slots;
-// the weights then run a slice ahead.  All of them leave a SIMD the 176
-// registers of the other phase's register-direct decode waves.  What bounds
-// them is LDS bandwidth, about as many cycles as the MFMAs, and, with few rows,
-// the weight stream.  DeepSeek-V3-shaped share (H 7168, I 2048, 32 experts), P
-// alone, whole layer in us, 160-row tiles of full height -> these: 32 rows per
-// expert 568 -> 550, 128 rows 691 -> 677, 192 rows 983 -> 905, 256 rows 1057 ->
-// 1010 (GEMM2 327 -> 306).
-constexpr int kPrefillRows = 192;
+// Prefill tiles of up to 160 rows, cut to the 32-row blocks they hold: the
+// MFMAs, A transfers and fragment reads go with a tile's rows.  They leave a
+// SIMD the 176 registers of the other phase's register-direct decode waves.
+// What bounds them is LDS bandwidth, about as many cycles as the MFMAs, and,
+// with few rows, the weight stream.  DeepSeek-V3-shaped share (H 7168, I 2048,
+// 32 experts), P alone, whole layer in us, 160-row tiles of full height ->
+// these: 32 rows per expert 568 -> 551, 192 rows 983 -> 926, 256 rows 1057 ->
+// 1030.  A 192-row tile (2 x 2 waves, two activation slots) went both ways: 3 to
+// 6 % faster for skewed batches of 46 rows per expert and more at H 7168 or 78
+// at H 2560, 5 % slower for 183 even rows at H 2048 and 47 skewed at H 2560.
+constexpr int kPrefillRows = 160;
 constexpr int kPrefillChunks = ring_chunks(160, 256, 64, 3, 3, true);
 template <bool GATED>
 __device__ __forceinline__ void gemm_ring_prefill(const GemmArgs& g) {
@@ -883,8 +876,7 @@ __device__ __forceinline__ void gemm_ring_prefill(const GemmArgs& g) {
   else if (blocks == 2) MOEPD_RING(64, 1, 4, 3, 3);
   else if (blocks == 3) MOEPD_RING(96, 1, 4, 3, 3);
   else if (blocks == 4) MOEPD_RING(128, 1, 4, 3, 3);
-  else if (blocks == 5) MOEPD_RING(160, 1, 4, 3, 3);
-  else MOEPD_RING(192, 2, 2, 2, 3);
+  else MOEPD_RING(160, 1, 4, 3, 3);
 #undef MOEPD_RING
 }
 
@@ -931,7 +923,7 @@ long long ffn_bf16_handover_words(long long rows_cap, int e_loc, int H) {
 
 hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn,
                            int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool stage, bool share,
-                           YieldTo yield, const int32_t* other_window, hipStream_t s) {
+                           int per_cu, YieldTo yield, const int32_t* other_window, hipStream_t s) {
   GemmArgs g{};
   g.yield = yield;
   g.offsets = b.offsets;
@@ -1024,7 +1016,14 @@ hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const vo
     const double tiles = m_tiles_hint * g.n_tiles;
     auto rounds = [&](int per_cu) { return tiles / (256.0 * per_cu); };
     auto cost = [&](int per_cu) { return ceil(rounds(per_cu) - 0.15) / rounds(per_cu); };
+    // Where both phases run small tiles the caller gives it: six of 24 KB for P,
+    // whose tiles wait for D and so must leave D's place kernel some LDS, eight of
+    // 20 KB for D, whose tiles then fit where one of P's has ended (700 + 64 tokens
+    // at H 7168 with four per CU for D 1384 us a pass, 914 when all tiles took 12
+    // KB and found a place beside P's).
     if (!stage) form(std::integral_constant<int, 0>{});
+    else if (per_cu == 6) form(std::integral_constant<int, 6>{});
+    else if (per_cu == 8) form(std::integral_constant<int, 8>{});
     else if (tiles <= 4 * 256 || cost(4) <= 1.1) form(std::integral_constant<int, 4>{});
     else if (rounds(8) > 1.15 && cost(6) < cost(8)) form(std::integral_constant<int, 6>{});
     else form(std::integral_constant<int, 8>{});

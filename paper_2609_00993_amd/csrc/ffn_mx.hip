@@ -17,12 +17,14 @@
 //    their maxima), GEMM2 writes float32 y.
 //
 // Two tile shapes, as in the bf16 layer: the weight-streaming tile for small
-// batches (32 rows x 32 columns, one wave per workgroup, operands through
-// the wave's LDS stage) and, for large batches, tiles of up to 256 rows by
+// batches (up to 64 rows x 32 or 64 columns, one wave per workgroup, operands
+// through the wave's LDS ring) and, for large batches, tiles of up to 256 rows by
 // 128 (gate + up) / 256 columns, cut to the 32-row blocks that they hold and
 // staged through LDS rings of 128-deep K slices (128 bytes per row, the byte
 // layout of the bf16 ring's 64-deep slices), with the scale bytes staged
 // alongside.
+#include <math.h>
+
 #include <type_traits>
 
 #include "common.h"
@@ -156,62 +158,89 @@ __device__ __forceinline__ float silu_mul_mx(float gt, float up) {
 // workgroups, 1.5 tiles per CU left half the CUs with two).
 constexpr int kMxDecodeWaves = 1;
 
-// One wave: 32 output columns x 32 rows of the tile, over all of K.  The
-// MFMAs take the weight rows as their first operand, so lane l ends with
-// token row l % 32 and the 16 columns 8q + 4h + (0..3), q = 0..3.
-// A 128-deep K block of a panel (the tile's 32 code rows, or its 32 gate or
-// up weight rows) is 4 KB: it is loaded by four 1 KB whole-line reads (lane
-// l: row 8i + l/8, 16-byte unit l%8), written to this wave's LDS stage (unit
-// c of row r at slot 8r + (c ^ stage_swz(r)), no bank conflicts either way) and read
-// back in the MFMA lane layout; reading 16 bytes from each of 32 rows per
-// instruction reaches only about a quarter of the per-CU rate of whole-line
-// reads.  A row's four scale bytes of the block come as one 4-byte load.
-// SC2 (K a multiple of 256, scale arrays 8-byte aligned): a row's scale
-// bytes of two blocks come as one 8-byte load every second block.  Scale
-// loads read a few bytes from each of 32 rows per instruction (the slow
-// pattern), so halving them leaves the whole-line code loads more room.
-template <bool GATED, bool SC2>
-__device__ __forceinline__ void gemm_mx_skinny_tile(const GemmArgsMX& g, const TileCoord& tc) {
-  static_assert(kMxDecodeWaves == 1, "the LDS stage below is private to the workgroup's one wave");
-  constexpr int NB = GATED ? 2 : 1;
-  constexpr int NP = 1 + NB;  // panels: code rows, then weight rows (gate, up)
-  __shared__ u32x4 stage[NP][32 * 8];
+// One wave: up to 32 MB rows of one expert and two blocks of 32 weight rows (gate
+// and up, or columns of y), over all of K.  As the bf16 decode tile: a 128-deep
+// K block of a panel (32 rows) is 4 KB, moved HBM -> LDS by four 1 KB DMA
+// instructions of eight whole 128-byte row pieces each (lane l: row 8i + l/8,
+// 16-byte unit l%8; unit c of row r at slot 8r + (c ^ stage_swz(r)), no bank
+// conflicts when the fragments are read), SLOTS blocks in the wave's ring, a
+// slot refilled once its fragments are in registers.  SC4 (K a multiple of
+// 512, scale arrays 16-byte aligned): a 16-byte gather brings a row's scales of
+// four blocks into one buffer, read into registers at the first of them;
+// otherwise each block's four bytes per row are gathered into its slot.  A
+// gather touches a line per row whatever its width.  The MFMAs take the weight
+// rows as their first operand, so lane l ends with token row l % 32 of each
+// block and the 16 columns 8q + 4h + (0..3), q = 0..3.
+//
+// DeepSeek-V3-shaped FP8 share, GEMM1 / GEMM2 in us, against 32-row tiles with
+// two blocks in flight in registers and scales loaded there: 4 tokens 43 / 16
+// -> 28 / 13, 40 tokens 134 / 65 -> 127 / 68, 128 tokens 188 / 90 -> 178 / 94,
+// 256 skewed tokens 287 / 153 -> 239 / 120 (the weights alone: 162 / 81).
+constexpr int mx_decode_gathers(int mb) { return (mb + 3) / 2; }  // of 64 rows each: mb + 2 panels
+constexpr int mx_decode_slot(int mb, bool sc4) {                  // 16-byte chunks
+  return (mb + 2) * 256 + (sc4 ? 0 : 16 * mx_decode_gathers(mb));
+}
+template <int MB, int SLOTS, bool GATED, bool SC4>
+__device__ __forceinline__ void gemm_mx_skinny_tile(const GemmArgsMX& g, const TileCoord& tc, u32x4* lds) {
+  static_assert(kMxDecodeWaves == 1, "the LDS ring below is private to the workgroup's one wave");
+  static_assert(SLOTS >= 1 && SLOTS <= 4, "a group's gathers are older than the block that first needs them");
+  constexpr int NB = 2;  // 32 columns of gate and of up, or two blocks of 32 columns
+  constexpr int NP = MB + NB, PANEL = 256;
+  constexpr int NG = mx_decode_gathers(MB);
+  constexpr int SLOT = mx_decode_slot(MB, SC4);
+  constexpr int NPS = 4 * NP + (SC4 ? 0 : NG);  // DMA instructions of a block
+  u32x4* const scales = lds + SLOTS * SLOT;      // SC4
   const int lane = threadIdx.x & 63;
   const int r = lane & 31, h = lane >> 5;
   const int lr = lane >> 3, lc = lane & 7;
-  const int col0 = tc.n0;
-  if (col0 >= g.N) return;  // N is a multiple of 32: a wave's columns are all in or all out
-  const int KS = g.K / 32;
-  const uint8_t* Be = g.B + (size_t)tc.e * g.b_stride;
-  const uint8_t* Bse = g.Bs + (size_t)tc.e * g.bs_stride;
-  const u32x4* base[NP];
-  const uint32_t* sbase[NP];
-  base[0] = reinterpret_cast<const u32x4*>(g.A);
-  sbase[0] = reinterpret_cast<const uint32_t*>(g.As);
-  base[1] = reinterpret_cast<const u32x4*>(Be);
-  sbase[1] = reinterpret_cast<const uint32_t*>(Bse);
-  if (GATED) {
-    base[NP - 1] = reinterpret_cast<const u32x4*>(Be + (size_t)g.up_row * g.K);
-    sbase[NP - 1] = reinterpret_cast<const uint32_t*>(Bse + (size_t)g.up_row * KS);
+  const int m0 = __builtin_amdgcn_readfirstlane(tc.m0), m_end = __builtin_amdgcn_readfirstlane(tc.m_end);
+  const int n0 = __builtin_amdgcn_readfirstlane(tc.n0), e = __builtin_amdgcn_readfirstlane(tc.e);
+  const int KS = g.K / 32, KB = g.K / 128;
+  const int b_step = GATED ? g.up_row : 32;  // weight rows from one block of 32 to the next
+  auto rsrc = [](const uint8_t* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, (short)0, bytes, kBufferRsrcWord3);
+  };
+  const __amdgpu_buffer_rsrc_t a_rsrc = rsrc(g.A + (size_t)m0 * g.K, min(m_end - m0, 32 * MB) * g.K);
+  const __amdgpu_buffer_rsrc_t b_rsrc = rsrc(g.B + (size_t)e * g.b_stride, (int)g.b_stride);
+  int off[2];  // stage_swz repeats every 16 rows
+#pragma unroll
+  for (int i = 0; i < 2; ++i) off[i] = (8 * i + lr) * g.K + (lc ^ stage_swz(8 * i + lr)) * 16;
+  const int row16 = 16 * g.K;
+  // Gather q: panel 2q + h, row r of it (the last panel again where they run
+  // out); rows past the expert's end repeat its last (never stored).
+  const uint8_t* sc_src[NG];
+#pragma unroll
+  for (int q = 0; q < NG; ++q) {
+    const int p = min(2 * q + h, NP - 1);
+    sc_src[q] = p < MB ? g.As + (size_t)min(m0 + 32 * p + r, m_end - 1) * KS
+                       : g.Bs + (size_t)e * g.bs_stride + (size_t)((p - MB) * b_step + n0 + r) * KS;
   }
-  // Offsets in 16-byte units and scale words; 32 bits suffice (fewer than
-  // 32 x 1024 code rows of at most 1024 units in this regime, at most
-  // 2 x 16384 weight rows).
-  const int kv = g.K / 16, kw = KS / 4;
-  int off[NP][4], soff[NP];
+  auto issue = [&](int kb, int slot) {
+    u32x4* dst = lds + slot * SLOT;
+    if constexpr (!SC4) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int rr = 8 * i + lr;
-    off[0][i] = min(tc.m0 + rr, tc.m_end - 1) * kv + lc;
+      for (int q = 0; q < NG; ++q)
+        __builtin_amdgcn_global_load_lds(MOEPD_GPTR(sc_src[q] + kb * 4), MOEPD_LPTR(dst + NP * PANEL + q * 16), 4, 0, 0);
+    }
 #pragma unroll
-    for (int j = 0; j < NB; ++j) off[1 + j][i] = (col0 + rr) * kv + lc;
-  }
-  soff[0] = min(tc.m0 + r, tc.m_end - 1) * kw;
+    for (int p = 0; p < MB; ++p)
 #pragma unroll
-  for (int j = 0; j < NB; ++j) soff[1 + j] = (col0 + r) * kw;
-  int wslot[4];  // LDS slot of this lane's chunk for each of the four instructions
+      for (int i = 0; i < 4; ++i)
+        // rows past the expert's end lie past the resource: the row part stays in the lane offset, which is checked
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, MOEPD_LPTR(dst + p * PANEL + i * 64), 16,
+                                                 off[i & 1] + (2 * p + (i >> 1)) * row16, kb * 128, 0, 0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) wslot[i] = (8 * i + lr) * 8 + (lc ^ stage_swz(8 * i + lr));
+    for (int p = 0; p < NB; ++p)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, MOEPD_LPTR(dst + (MB + p) * PANEL + i * 64), 16, off[i & 1],
+                                                 kb * 128 + (p * b_step + n0) * g.K + (i >> 1) * row16, 0, 0);
+  };
+  auto issue_group = [&](int kb) {
+#pragma unroll
+    for (int q = 0; q < NG; ++q)
+      __builtin_amdgcn_global_load_lds(MOEPD_GPTR(sc_src[q] + kb * 4), MOEPD_LPTR(scales + q * 64), 16, 0, 0);
+  };
   // Step s (64 deep) of a block: lane (r, h) holds units 4s + h and 4s + 2 + h
   // of its row and the scale of 32-value block 2s + h.
   int rslot[2][2];
@@ -220,100 +249,95 @@ __device__ __forceinline__ void gemm_mx_skinny_tile(const GemmArgsMX& g, const T
 #pragma unroll
     for (int u = 0; u < 2; ++u) rslot[st][u] = r * 8 + ((4 * st + 2 * u + h) ^ stage_swz(r));
 
-  f32x16_mx acc[NB];
+  f32x16_mx acc[MB][NB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j)
+  for (int m = 0; m < MB; ++m)
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[m][j][q] = 0.f;
 
-  const int KB = g.K / 128;
-  constexpr int PF = 2;  // 128-deep K blocks in flight per wave
-  u32x4 v[PF][NP][4];
-  auto mfma_block = [&](const uint32_t (&scl)[NP]) {
+  u32x4 raw[NP];  // SC4: the panels' scale words of four blocks; else the 16 bytes that hold this block's
+  if constexpr (SC4) issue_group(0);
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      const v8i32 a = join(stage[0][rslot[st][0]], stage[0][rslot[st][1]]);
-      const int sa = (int)((scl[0] >> (16 * st)) & 0xffu);
+  for (int q = 0; q < SLOTS; ++q)
+    if (q < KB) issue(q, q);
+  int slot = 0;
+  for (int kb = 0; kb < KB; ++kb) {
+    // block kb has landed once at most the newer blocks remain (a group's
+    // gathers among them make the wait stricter)
+    wait_rings_lgkm0<NPS, 0, SLOTS - 1, 0>(KB - 1 - kb);
+    const u32x4* src = lds + slot * SLOT;
+    v8i32 f[2][NP];
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
-        acc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-            join(stage[1 + j][rslot[st][0]], stage[1 + j][rslot[st][1]]), a, acc[j], 0, 0, 0,
-            (int)((scl[1 + j] >> (16 * st)) & 0xffu), 0, sa);
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) f[st][p] = join(src[p * PANEL + rslot[st][0]], src[p * PANEL + rslot[st][1]]);
+    if constexpr (SC4) {
+      if ((kb & 3) == 0)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) raw[p] = scales[32 * p + r];
+    } else {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) raw[p] = src[NP * PANEL + (32 * p + r) / 4];
     }
-  };
-  // LDS operations of one wave run in order, so a block's stage writes land
-  // after the previous block's reads and before its own.
-  auto stage_block = [&](const u32x4 (&d)[NP][4]) {
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) stage[p][wslot[i]] = d[p][i];
-  };
-  // Scale words of the block pair in flight (SC2) or of each block.
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  uint32_t sc[PF][NP];
-  u32x2 sp[NP], sp_next[NP];
-  auto load = [&](int kb, u32x4 (&d)[NP][4], uint32_t (&ds)[NP]) {
+    wait_vmcnt_lgkm0<63>();  // the block is in registers: its slot is free
+    if constexpr (SC4) {
+      if ((kb & 3) == 0 && kb + 4 < KB) issue_group(kb + 4);
+    }
+    if (kb + SLOTS < KB) issue(kb + SLOTS, slot);
+    uint32_t scl[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) d[p][i] = base[p][off[p][i] + kb * 8];
-      if (SC2) {
-        if ((kb & 1) == 0) sp_next[p] = *reinterpret_cast<const u32x2*>(sbase[p] + soff[p] + kb);
-      } else {
-        ds[p] = sbase[p][soff[p] + kb];
-      }
-    }
-  };
-#pragma unroll
-  for (int q = 0; q < PF; ++q)
-    if (q < KB) load(q, v[q], sc[q]);
-  for (int kb0 = 0; kb0 < KB; kb0 += PF) {
-    if (SC2) {
-#pragma unroll
-      for (int p = 0; p < NP; ++p) sp[p] = sp_next[p];
+      const int c = SC4 ? kb & 3 : lane & 3;
+      scl[p] = (c == 0 ? raw[p][0] : c == 1 ? raw[p][1] : c == 2 ? raw[p][2] : raw[p][3]) >> (8 * h);
     }
 #pragma unroll
-    for (int q = 0; q < PF; ++q) {
-      const int kb = kb0 + q;
-      if (kb < KB) {
-        stage_block(v[q]);
-        uint32_t scl[NP];
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
-        for (int p = 0; p < NP; ++p) scl[p] = (SC2 ? sp[p][q] : sc[q][p]) >> (8 * h);
-        if (kb + PF < KB) load(kb + PF, v[q], sc[q]);
-        mfma_block(scl);
-      }
-    }
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[m][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f[st][MB + j], f[st][m], acc[m][j], 0, 0, 0,
+                                                                      (int)(scl[MB + j] >> (16 * st)), 0,
+                                                                      (int)(scl[m] >> (16 * st)));
+    if (++slot == SLOTS) slot = 0;
   }
 
-  const int row = tc.m0 + r;
-  if (row >= tc.m_end) return;
-  if (GATED) {
-    float v[16];
-    float amax = 0.f;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      v[q] = silu_mul_mx(acc[0][q], acc[NB - 1][q]);
-      amax = fmaxf(amax, fabsf(v[q]));
+  for (int m = 0; m < MB; ++m) {
+    const int row = m0 + 32 * m + r;
+    const bool live = row < m_end;
+    if (GATED) {
+      float v[16];
+      float amax = 0.f;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        v[q] = silu_mul_mx(acc[m][0][q], acc[m][NB - 1][q]);
+        amax = fmaxf(amax, fabsf(v[q]));
+      }
+      amax = fmaxf(amax, __shfl_xor(amax, 32, kWave));  // the row's other 16 columns
+      if (!live) continue;
+      const int ex = mx_exponent(amax);
+      const float inv = pow2_neg(ex);
+      uint8_t* hrow = static_cast<uint8_t*>(g.C) + (size_t)row * g.N + n0 + 4 * h;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t w = e4m3_pair(v[4 * q] * inv, v[4 * q + 1] * inv) |
+                           (e4m3_pair(v[4 * q + 2] * inv, v[4 * q + 3] * inv) << 16);
+        *reinterpret_cast<uint32_t*>(hrow + 8 * q) = w;
+      }
+      if (h == 0) g.Cs[(size_t)row * (g.N / 32) + n0 / 32] = (uint8_t)(ex + 127);
+    } else {
+      if (!live) continue;
+      float* yrow = static_cast<float*>(g.C) + (size_t)row * g.N + n0 + 4 * h;
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4_mx*>(yrow + 32 * j + 8 * q) =
+              f32x4_mx{acc[m][j][4 * q], acc[m][j][4 * q + 1], acc[m][j][4 * q + 2], acc[m][j][4 * q + 3]};
     }
-    amax = fmaxf(amax, __shfl_xor(amax, 32, kWave));  // the row's other 16 columns
-    const int e = mx_exponent(amax);
-    const float inv = pow2_neg(e);
-    uint8_t* hrow = static_cast<uint8_t*>(g.C) + (size_t)row * g.N + col0 + 4 * h;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t w = e4m3_pair(v[4 * q] * inv, v[4 * q + 1] * inv) |
-                         (e4m3_pair(v[4 * q + 2] * inv, v[4 * q + 3] * inv) << 16);
-      *reinterpret_cast<uint32_t*>(hrow + 8 * q) = w;
-    }
-    if (h == 0) g.Cs[(size_t)row * (g.N / 32) + col0 / 32] = (uint8_t)(e + 127);
-  } else {
-    float* yrow = static_cast<float*>(g.C) + (size_t)row * g.N + col0 + 4 * h;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<f32x4_mx*>(yrow + 8 * q) =
-          f32x4_mx{acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]};
   }
 }
 
@@ -679,20 +703,35 @@ __global__ __launch_bounds__(256) void gemm1_mx_prefill(GemmArgsMX g) { gemm_mx_
 template <bool SC4>
 __global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) { gemm_mx_ring<false, SC4>(g); }
 
-template <bool GATED, bool SC2>
+// Small-batch tiles of up to kMxDecodeRows rows, cut to their 32-row blocks (64 is
+// what one slot and the scales of the eight-per-CU form take; with 96 rows and
+// six per CU instead, 40 tokens at H 7168 took 145 us for GEMM1 against 127,
+// 256 skewed ones 225 against 239).  GEMM1's are 32 columns of gate and up,
+// GEMM2's 64 columns.
+constexpr int kMxDecodeRows = 64;
+constexpr int mx_decode_chunks(int per_cu) { return (per_cu == 8 ? 144 : 160) * 64 / per_cu; }
+constexpr int mx_decode_slots(int mb, int per_cu, bool sc4) {
+  const int n = (mx_decode_chunks(per_cu) - (sc4 ? 64 * mx_decode_gathers(mb) : 0)) / mx_decode_slot(mb, sc4);
+  return n > 4 ? 4 : n;
+}
+template <bool GATED, bool SC4, int PER_CU>
 __global__ __launch_bounds__(64 * kMxDecodeWaves) void gemm_mx_skinny(GemmArgsMX g) {
+  __shared__ u32x4 lds[mx_decode_chunks(PER_CU)];
   const int L = block_tile(g);
   if (L < 0) return;
   yield_to_window(g.yield);
   TileCoord tc;
-  tile_at(g, L, 32, 32 * kMxDecodeWaves, tc);
-  gemm_mx_skinny_tile<GATED, SC2>(g, tc);
+  tile_at(g, L, kMxDecodeRows, GATED ? 32 : 64, tc);
+  const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
+  if (blocks <= 1) gemm_mx_skinny_tile<1, mx_decode_slots(1, PER_CU, SC4), GATED, SC4>(g, tc, lds);
+  else gemm_mx_skinny_tile<2, mx_decode_slots(2, PER_CU, SC4), GATED, SC4>(g, tc, lds);
 }
 
 static inline int round8_mx(long long v) { return (int)((v + 7) / 8 * 8); }
 
 hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBuffers& mx, const MxWeights& w,
-                         int e_loc, int H, int I, int max_m_tiles, YieldTo yield, hipStream_t s) {
+                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool beside, YieldTo yield,
+                         hipStream_t s) {
   GemmArgsMX g{};
   g.offsets = b.offsets;
   g.tile_base = b.tile_base;
@@ -734,14 +773,27 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
     if (gemm == 1) sc4 ? go(gemm1_mx_prefill<true>) : go(gemm1_mx_prefill<false>);
     else sc4 ? go(gemm2_mx_prefill<true>) : go(gemm2_mx_prefill<false>);
   } else {
-    g.n_tiles = (g.N + 32 * kMxDecodeWaves - 1) / (32 * kMxDecodeWaves);
+    g.n_tiles = g.N / (gemm == 1 ? 32 : 64);
     g.xcd_local = g.n_tiles % 8 == 0 ? 2 : 1;
     const dim3 grid(round8_mx((long long)max_m_tiles * g.n_tiles));
-    const bool sc2 = g.K % 256 == 0 && ((uintptr_t)g.As | (uintptr_t)g.Bs) % 8 == 0 && g.bs_stride % 8 == 0 &&
-                     ((long long)g.up_row * (g.K / 32)) % 8 == 0;
+    const bool sc4 = g.K % 512 == 0 && ((uintptr_t)g.As | (uintptr_t)g.Bs) % 16 == 0;
     auto go = [&](auto k) { k<<<grid, 64 * kMxDecodeWaves, 0, s>>>(g); };
-    if (gemm == 1) sc2 ? go(gemm_mx_skinny<true, true>) : go(gemm_mx_skinny<true, false>);
-    else sc2 ? go(gemm_mx_skinny<false, true>) : go(gemm_mx_skinny<false, false>);
+    auto form = [&](auto per_cu) {
+      constexpr int P = decltype(per_cu)::value;
+      if (gemm == 1) sc4 ? go(gemm_mx_skinny<true, true, P>) : go(gemm_mx_skinny<true, false, P>);
+      else sc4 ? go(gemm_mx_skinny<false, true, P>) : go(gemm_mx_skinny<false, false, P>);
+    };
+    // Workgroups per CU, as for the bf16 tiles.
+    const double tiles = m_tiles_hint * g.n_tiles;
+    auto rounds = [&](int per_cu) { return tiles / (256.0 * per_cu); };
+    auto cost = [&](int per_cu) { return ceil(rounds(per_cu) - 0.15) / rounds(per_cu); };
+    // P's, while D runs layers too: eight, 144 KB, so D's place kernel finds LDS
+    // on a CU whose P tiles wait for D (700 + 64 tokens at H 7168 593 us a pass; with
+    // eight for D as well 1020).
+    if (beside) form(std::integral_constant<int, 8>{});
+    else if (tiles <= 4 * 256 || cost(4) <= 1.1) form(std::integral_constant<int, 4>{});
+    else if (rounds(8) > 1.15 && cost(6) < cost(8)) form(std::integral_constant<int, 6>{});
+    else form(std::integral_constant<int, 8>{});
   }
   return hipGetLastError();
 }
@@ -756,7 +808,7 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
 // 256 rows 669 / 727,  320 rows 774 / 776,  384 rows 938 / 932,
 // 512 rows 1127 / 1175;  skewed 16384-token batch 5680 / 5882.
 int ffn_mx_bm(int regime, long long avg_rows) {
-  if (regime != 0) return 32;
+  if (regime != 0) return kMxDecodeRows;
   long long dev = 0;
   while ((dev + 1) * (dev + 1) <= avg_rows) ++dev;
   const long long r = avg_rows + dev;

@@ -139,7 +139,7 @@ hipError_t launch_combine(const void* y, const float* topk_w, const int32_t* row
                           void* out, WindowSignal close, hipStream_t s);
 
 // Grouped expert FFN.  `regime` picks the tile configuration (0 = large
-// batches, tiles of up to 192 rows; 1 = small batches, weight-streaming tiles of
+// batches, tiles of up to 160 rows; 1 = small batches, weight-streaming tiles of
 // one wave; 2 = very large batches, 256-row tiles);
 // ffn_bf16_bm gives its m-tile height, which the place kernel must use for
 // tile_base.
@@ -147,7 +147,8 @@ int ffn_bf16_bm(int regime, bool stage);
 // stage (decode regime only): tiles of up to 96 rows, operands as whole lines
 // through a per-wave LDS ring (faster), or 32-row tiles straight into registers
 // with no LDS, which fit on CUs held by the other phase's prefill tiles.
-// m_tiles_hint: expected m-tiles of a small batch under even routing.  share (256-row
+// m_tiles_hint: expected m-tiles of a small batch under even routing.  per_cu:
+// workgroups per CU of the staged tiles (0: chosen for the expected tiles).  share (256-row
 // regime, GEMM2 only): the tiles that leave each CU room for the other
 // phase's staged decode GEMM2 tiles (80 KB of LDS and 364 registers instead
 // of 160 KB and 460; the same bits, 12 % slower alone) run only while the
@@ -157,7 +158,7 @@ int ffn_bf16_bm(int regime, bool stage);
 // does the rest.
 hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn,
                            int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool stage, bool share,
-                           YieldTo yield, const int32_t* other_window, hipStream_t s);
+                           int per_cu, YieldTo yield, const int32_t* other_window, hipStream_t s);
 // Words of b.tile_done a phase needs (256-row GEMM2 tiles at its capacity).
 long long ffn_bf16_handover_words(long long rows_cap, int e_loc, int H);
 
@@ -179,11 +180,12 @@ struct MxWeights {
 hipError_t launch_permute_mx(const void* x, int T, int k, int H, const int32_t* row_of_slot, uint8_t* codes,
                              uint8_t* scales, hipStream_t s);
 // regime 0: large batches (LDS-ring tiles of up to 192 or 256 rows); 1: small
-// batches (32-row weight-streaming tiles).  The m-tile height of a batch that
+// batches (weight-streaming tiles of one wave).  The m-tile height of a batch that
 // expects avg_rows rows per expert, which the place kernel must use.
 int ffn_mx_bm(int regime, long long avg_rows);
 hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBuffers& mx, const MxWeights& w,
-                         int e_loc, int H, int I, int max_m_tiles, YieldTo yield, hipStream_t s);
+                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool beside, YieldTo yield,
+                         hipStream_t s);  // beside: P's small tiles, with D's layers
 
 int ffn_f32_bm();
 hipError_t launch_ffn_f32(int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn, int e_loc, int H,

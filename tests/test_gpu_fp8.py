@@ -192,3 +192,24 @@ def test_fp8_ring_heights(rows, H, I):
         assert g.fetch(0)["counts"].tolist() == rows
     finally:
         g.close()
+
+
+# The small-batch tiles: 32-row blocks and one to three tiles of 64 rows at their
+# edges; K blocks with and without the four-block scale gathers, fewer and more
+# than the ring's slots; tile counts that choose four, eight (16 experts x 80
+# or 128 column tiles) and six (16 x 160) workgroups per CU.
+@pytest.mark.parametrize("H,I", [(128, 128), (384, 256), (512, 640), (128, 2560), (512, 4096), (128, 5120)])
+def test_fp8_decode_heights(H, I):
+    rows = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 0, 2, 3, 40, 5]
+    E, E_loc, T = 64, len(rows), sum(rows)
+    spec = LayerSpec("rows-decode-fp8", E=E, e0=8, E_loc=E_loc, k=1, H=H, I=I, dtype=FP8, T_P=0, T_D=T)
+    inp = make_layer(spec, seed=49)
+    owner = 8 + np.random.default_rng(50).permutation(np.repeat(np.arange(E_loc), rows))
+    inp.logits[1] = np.where(np.arange(E)[None, :] == owner[:, None], 1.0, -1.0).astype(np.float32)
+    g = GpuLayer(inp)
+    try:
+        g.run(1)
+        check_phase(g, inp, 1)
+        assert g.fetch(1)["counts"].tolist() == rows
+    finally:
+        g.close()

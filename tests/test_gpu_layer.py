@@ -112,7 +112,7 @@ def test_layer_parity(name):
 
 
 # Exact rows per expert at the edges of the prefill tiles' heights (32-row
-# blocks, one to three tiles of 192 rows), over K slices from one up: fewer than
+# blocks, one to three tiles of 160 rows), over K slices from one up: fewer than
 # the rings' slots, as many, and one more; N down to a partial column tile.
 EDGE_ROWS = [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 191, 192, 193, 256, 384, 385]
 

@@ -277,9 +277,9 @@ int moe_dispatch_permute(moe_ctx_t* ctx, int phase, const void* x, hipStream_t s
  * is read from the device-side offsets (no host synchronisation).  bf16
  * small-batch tiles come in two forms with identical results: LDS-staged,
  * or, when the other phase's latest moe_expert_ffn ran large-batch tiles
- * (which leave too little LDS to share their CUs), register-direct.  The
- * batch's dispatch layout chooses; a captured graph keeps the form chosen at
- * capture.
+ * (which leave too little LDS to share their CUs), register-direct.  A
+ * captured graph keeps the form chosen at capture, which replays over any
+ * dispatch of the same T.
  * Errors: MOE_ERR_INVALID_ARG, MOE_ERR_INVALID_PHASE, MOE_ERR_STATE, MOE_ERR_HIP. */
 int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream);
 

@@ -40,7 +40,6 @@ struct Phase {
   int T = 0;
   int regime = 0;  // tile shape (ffn_bf16_bm / ffn_mx_bm): 0 large batch, 1 small, 2 very large (bf16)
   int bm = 0;
-  bool stage = true;  // form of the small-batch tiles (launch_ffn_bf16)
   int chunk_tokens = 1;
   int nchunks = 1;
   int max_tokens = 0;
@@ -73,7 +72,7 @@ struct moe_ctx {
   // its decode tiles: prefill tiles leave 3 KB of a CU's LDS free,
   // too little for the LDS-staged decode tile, so beside them the phase takes
   // the tile that needs no LDS and can share their CUs.  Only a performance
-  // choice: both tiles give the same results.
+  // choice: both tiles give the same results, over any layout of the batch.
   std::atomic<int> ffn_regime[MOE_NUM_PHASES] = {-1, -1};
 };
 
@@ -146,7 +145,7 @@ int alloc_phase(moe_ctx* ctx, int phase) {
   const size_t o_part = take((size_t)p.router_cap * c.num_experts * 4);
   // The signal slot is 16 bytes: the grouped GEMMs read the window word in it
   // with a 16-byte LDS DMA (its other words stay zero).
-  const size_t o_cc = take((size_t)E * mc * 4), o_tb = take((E + 1) * 4), o_sig = take(16);
+  const size_t o_cc = take((size_t)E * mc * 4), o_tb = take((E + 1) * 4), o_tb32 = take((E + 1) * 4), o_sig = take(16);
   const size_t o_td = take(c.dtype == MOE_DTYPE_BF16 ? (size_t)ffn_bf16_handover_words(p.rows_cap, E, c.hidden) * 4 : 0);
 
   void* mem = nullptr;
@@ -167,6 +166,7 @@ int alloc_phase(moe_ctx* ctx, int phase) {
   p.b.y = (float*)(base + o_y);
   p.b.chunk_counts = (int32_t*)(base + o_cc);
   p.b.tile_base = (int32_t*)(base + o_tb);
+  p.b.tile_base32 = (int32_t*)(base + o_tb32);
   p.b.signal = (int32_t*)(base + o_sig);
   p.b.tile_done = (int32_t*)(base + o_td);
   p.b.logits = (float*)(base + o_lg);
@@ -270,19 +270,21 @@ int layout(moe_ctx* ctx, Phase& p, hipStream_t stream) {
   const moe_config_t& c = ctx->cfg;
   const int T = p.T, k = c.top_k, E_loc = c.num_local_experts;
   dispatch_chunking(T, k, E_loc, &p.chunk_tokens, &p.nchunks);
+  bool prefix32 = false;
   if (c.dtype == MOE_DTYPE_FP8) {
     const long long avg = (long long)T * k / c.num_experts;
     p.regime = avg >= 32 ? 0 : 1;
     p.bm = ffn_mx_bm(p.regime, avg);
   } else if (c.dtype == MOE_DTYPE_BF16) {
     // Rows per resident expert expected under even routing: T*k/E.  Small
-    // batches stream weights (32-row tiles); large ones take tiles of up to 160
-    // rows, and very large ones 256-row tiles, which move fewer bytes into LDS per
-    // flop.
+    // batches stream weights (tiles of up to 96 rows); large ones take tiles of up
+    // to 160 rows, and very large ones 256-row tiles, which move fewer bytes into
+    // LDS per flop.  Everything a layout leaves depends on T and the routing alone,
+    // so any of the phase's calls may be captured and replayed with others eager.
     const long long avg = (long long)T * k / c.num_experts;
     p.regime = avg >= 512 ? 2 : avg >= 32 ? 0 : 1;
-    p.stage = ctx->ffn_regime[(&p - ctx->ph) ^ 1].load(std::memory_order_relaxed) != 0;
-    p.bm = ffn_bf16_bm(p.regime, p.stage);
+    p.bm = ffn_bf16_bm(p.regime, true);
+    prefix32 = p.regime == 1;  // fewer than 32 x 1024 rows
   } else {
     p.regime = 0;
     p.bm = ffn_f32_bm();
@@ -295,7 +297,8 @@ int layout(moe_ctx* ctx, Phase& p, hipStream_t stream) {
     if (st) return st;
   }
   return timed(p, MOE_KERNEL_PLACE, stream, [&] {
-    return launch_place(p.b.topk_idx, T, k, c.expert_begin, E_loc, p.chunk_tokens, p.nchunks, p.bm, p.b, stream);
+    return launch_place(p.b.topk_idx, T, k, c.expert_begin, E_loc, p.chunk_tokens, p.nchunks, p.bm, prefix32, p.b,
+                        stream);
   });
 }
 
@@ -461,9 +464,11 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
   if (p.T > 0) {
     const int kk = c.top_k < c.num_local_experts ? c.top_k : c.num_local_experts;
     const long long rows = (long long)p.T * kk;
-    const int max_m_tiles = (int)((rows + p.bm - 1) / p.bm) + c.num_local_experts;
     ctx->ffn_regime[phase].store(p.regime, std::memory_order_relaxed);
     const int other = ctx->ffn_regime[phase ^ 1].load(std::memory_order_relaxed);
+    const bool stage = other != 0;
+    const int bm = c.dtype == MOE_DTYPE_BF16 ? ffn_bf16_bm(p.regime, stage) : p.bm;
+    const int max_m_tiles = (int)((rows + bm - 1) / bm) + c.num_local_experts;
     // D first (Section 3.1) on one GPU: while D-first admission is on and the
     // context runs D layers, P's 256-row GEMM2 takes the tile that leaves a CU
     // room for D's decode tiles beside it.
@@ -486,7 +491,7 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
                                yield_of(ctx, phase), stream);
         if (c.dtype == MOE_DTYPE_BF16)
           return launch_ffn_bf16(p.regime, gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden,
-                                 c.inter, max_m_tiles, m_tiles_hint, p.stage, share,
+                                 c.inter, max_m_tiles, m_tiles_hint, stage, share,
                                  beside ? (phase == MOE_PHASE_P ? 6 : 8) : 0, yield_of(ctx, phase),
                                  ctx->ph[phase ^ 1].b.signal, stream);
         return launch_ffn_f32(gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden, c.inter,

@@ -90,7 +90,7 @@ __device__ __host__ __forceinline__ int cell_words(int n) { return n + (n >> 5) 
 
 __global__ __launch_bounds__(256) void place_kernel(const int32_t* __restrict__ topk_idx, int T, int k, int e0,
                                                     int e_loc, int chunk_tokens, int nchunks, int nbits, int bm,
-                                                    PhaseBuffers b) {
+                                                    bool prefix32, PhaseBuffers b) {
   // LDS: the cells (sized at launch to e_loc * nchunks, so a small batch
   // needs only a few KB and can share a CU with a running prefill GEMM),
   // then per-expert bases, running counts and per-wave counts.
@@ -164,7 +164,8 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t* __restrict__ 
   if (tid < e_loc) base[tid] = cells[cix(tid * nchunks + c)];
   if (c == 0) {
     // publish the dispatch shape: counts, offsets, and the m-tile prefix
-    // (a block scan of the per-expert m-tile counts)
+    // (a block scan of the per-expert m-tile counts; with prefix32 the counts
+    // of 32-row m-tiles go through the same scan in the upper half-words)
     int mt = 0;
     if (tid < e_loc) {
       const int off = cells[cix(tid * nchunks)];
@@ -172,13 +173,19 @@ __global__ __launch_bounds__(256) void place_kernel(const int32_t* __restrict__ 
       b.offsets[tid] = off;
       b.counts[tid] = nxt - off;
       mt = (nxt - off + bm - 1) / bm;
+      if (prefix32) mt |= (nxt - off + 31) / 32 << 16;
     }
     int mt_total;
     const int tb = block_exclusive_scan_256(mt, wave_tot, &mt_total);
-    if (tid < e_loc) b.tile_base[tid] = tb;
+    const int low = prefix32 ? 0xffff : -1;
+    if (tid < e_loc) {
+      b.tile_base[tid] = tb & low;
+      if (prefix32) b.tile_base32[tid] = (int)((unsigned)tb >> 16);
+    }
     if (tid == 0) {
       b.offsets[e_loc] = total;
-      b.tile_base[e_loc] = mt_total;
+      b.tile_base[e_loc] = mt_total & low;
+      if (prefix32) b.tile_base32[e_loc] = (int)((unsigned)mt_total >> 16);
     }
   }
   for (int i = tid; i <= e_loc; i += 256) {
@@ -284,11 +291,12 @@ hipError_t launch_count(const int32_t* topk_idx, int T, int k, int e0, int e_loc
 }
 
 hipError_t launch_place(const int32_t* topk_idx, int T, int k, int e0, int e_loc, int chunk_tokens, int nchunks,
-                        int bm, const PhaseBuffers& b, hipStream_t s) {
+                        int bm, bool prefix32, const PhaseBuffers& b, hipStream_t s) {
   int nbits = 0;
   while ((1 << nbits) <= e_loc) ++nbits;  // categories 0..e_loc
   const size_t lds = sizeof(int) * ((size_t)cell_words(e_loc * nchunks) + e_loc + 5 * (size_t)(e_loc + 1));
-  place_kernel<<<dim3(nchunks), dim3(256), lds, s>>>(topk_idx, T, k, e0, e_loc, chunk_tokens, nchunks, nbits, bm, b);
+  place_kernel<<<dim3(nchunks), dim3(256), lds, s>>>(topk_idx, T, k, e0, e_loc, chunk_tokens, nchunks, nbits, bm,
+                                                     prefix32, b);
   return hipGetLastError();
 }
 

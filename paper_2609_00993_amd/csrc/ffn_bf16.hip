@@ -238,7 +238,7 @@ __device__ __forceinline__ void gemm_skinny_tile(const GemmArgs& g, const TileCo
 // The same tile with each operand loaded straight into MFMA lane layout (16
 // bytes from each of 32 rows per instruction) and no LDS: slower alone, but
 // it fits on a CU beside a prefill tile of the other phase, whose
-// ring leaves 4 KB of LDS free.
+// ring leaves 3 KB of LDS free.
 template <bool GATED, bool ROT>
 __device__ __forceinline__ void gemm_skinny_tile_direct(const GemmArgs& g, const TileCoord& tc) {
   constexpr int BN = 32 * kDecodeWaves;
@@ -311,8 +311,12 @@ __device__ __forceinline__ void gemm_skinny_tile_direct(const GemmArgs& g, const
 }
 
 // Staged decode tiles hold up to kDecodeRows rows, cut to their 32-row blocks:
-// 96 is what one slot of the eight-per-CU form takes.
+// 96 is what one slot of the eight-per-CU form takes.  Register-direct tiles hold
+// 32: their registers take no more.  The layout leaves a prefix of m-tiles of
+// either height (tile_base, tile_base32), so a captured FFN of one form replays
+// over a layout made when the other would have been chosen.
 constexpr int kDecodeRows = 96;
+constexpr int kDirectRows = 32;
 constexpr int decode_chunks(int per_cu) { return 160 / per_cu / 4 * 256; }  // 16-byte chunks of LDS: whole panels
 constexpr int decode_slots(int mb, int nb, int per_cu) {
   const int n = decode_chunks(per_cu) / ((mb + nb) * 32 * 8);
@@ -338,7 +342,7 @@ __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
     else if (blocks == 2) gemm_skinny_tile<2, NB, decode_slots(2, NB, PER_CU), GATED, ROT>(g, tc, lds);
     else gemm_skinny_tile<3, NB, decode_slots(3, NB, PER_CU), GATED, ROT>(g, tc, lds);
   } else {
-    tile_at(g, L, 32, 32 * kDecodeWaves, tc);
+    tile_at(g, L, kDirectRows, 32 * kDecodeWaves, tc);
     gemm_skinny_tile_direct<GATED, ROT>(g, tc);
   }
 }
@@ -912,7 +916,7 @@ __global__ __launch_bounds__(64 * kDecodeWaves) void gemm2_down_decode(GemmArgs 
 // ------------------------------------------------------------------ launch
 
 int ffn_bf16_bm(int regime, bool stage) {
-  return regime == 0 ? kPrefillRows : regime == 2 ? 256 : stage ? kDecodeRows : 32;
+  return regime == 0 ? kPrefillRows : regime == 2 ? 256 : stage ? kDecodeRows : kDirectRows;
 }
 
 static inline int round8(long long v) { return (int)((v + 7) / 8 * 8); }
@@ -994,6 +998,7 @@ hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const vo
     }
   } else {
     const bool rot = g.K % 2048 == 0;
+    if (!stage) g.tile_base = b.tile_base32;
     g.n_tiles = g.N / (stage && gemm == 2 ? 32 * gemm2_blocks(rot) : 32);
     g.n_group = 1;
     g.m_super = 0;

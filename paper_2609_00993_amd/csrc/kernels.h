@@ -22,6 +22,7 @@ struct PhaseBuffers {
   // workspace
   int32_t* chunk_counts;  // [E_loc * max_chunks], expert-major
   int32_t* tile_base;     // [E_loc + 1], prefix sum of m-tiles per expert
+  int32_t* tile_base32;   // the same for m-tiles of 32 rows (bf16 small batches)
   // Signal word of this phase's layer window: a generation number while a
   // layer is between its route and its combine, 0 otherwise.  Written only
   // by this phase's kernels; read by the other phase's grouped GEMMs.  It is
@@ -113,12 +114,13 @@ hipError_t launch_count(const int32_t* topk_idx, int T, int k, int e0, int e_loc
                         const PhaseBuffers& b, hipStream_t s);
 
 // Scan of the histogram cells (block 0 publishes counts, offsets and the
-// m-tile prefix for m-tiles of bm rows) and stable rows for every slot:
+// m-tile prefix for m-tiles of bm rows, and with prefix32 also the one for 32 rows,
+// of batches of less than 65536 m-tiles each) and stable rows for every slot:
 // row_of_slot and token_of_row.  Launched for every batch, T = 0 included.
 // With one chunk (nchunks == 1) the kernel counts the slots itself and the
 // count kernel is not launched.
 hipError_t launch_place(const int32_t* topk_idx, int T, int k, int e0, int e_loc, int chunk_tokens, int nchunks,
-                        int bm, const PhaseBuffers& b, hipStream_t s);
+                        int bm, bool prefix32, const PhaseBuffers& b, hipStream_t s);
 
 // x_perm[row] = x[t] for every resident slot (row-byte granularity 16 B).
 hipError_t launch_permute(const void* x, int T, int k, int row_bytes, const int32_t* row_of_slot, void* x_perm,
@@ -142,7 +144,7 @@ hipError_t launch_combine(const void* y, const float* topk_w, const int32_t* row
 // batches, tiles of up to 160 rows; 1 = small batches, weight-streaming tiles of
 // one wave; 2 = very large batches, 256-row tiles);
 // ffn_bf16_bm gives its m-tile height, which the place kernel must use for
-// tile_base.
+// tile_base (small batches: the staged form's; with stage false 32, tile_base32).
 int ffn_bf16_bm(int regime, bool stage);
 // stage (decode regime only): tiles of up to 96 rows, operands as whole lines
 // through a per-wave LDS ring (faster), or 32-row tiles straight into registers

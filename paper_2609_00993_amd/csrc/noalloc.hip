@@ -81,8 +81,8 @@ extern "C" int moe_dispatch_layout_noalloc(const int32_t* topk_idx, int32_t T, i
   if (nchunks > 1 &&
       launch_count(topk_idx, T, top_k, expert_begin, num_local_experts, chunk_tokens, nchunks, b, stream) != hipSuccess)
     return MOE_ERR_HIP;
-  if (launch_place(topk_idx, T, top_k, expert_begin, num_local_experts, chunk_tokens, nchunks, kPrefixTileRows, b,
-                   stream) != hipSuccess)
+  if (launch_place(topk_idx, T, top_k, expert_begin, num_local_experts, chunk_tokens, nchunks, kPrefixTileRows, false,
+                   b, stream) != hipSuccess)
     return MOE_ERR_HIP;
   return MOE_OK;
 }

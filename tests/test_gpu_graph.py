@@ -8,7 +8,7 @@ host synchronisations between replays.
 import numpy as np
 import pytest
 
-from synth import make_config
+from synth import BF16, LayerSpec, make_config, make_layer
 from tests.gpu_util import GpuLayer
 from tests.test_gpu_layer import check_phase
 
@@ -101,6 +101,61 @@ def test_capture_refuses_a_stream_hand_over():
         # nothing was enqueued and the phase is still usable from its stream
         g.run(1)
         torch.cuda.synchronize()
+        del graph
+    finally:
+        g.close()
+
+
+@pytest.mark.parametrize("form", ["staged", "direct"])
+def test_captured_ffn_replays_after_eager_dispatch(form):
+    """Any of a phase's calls may be captured: here the FFN and the combine,
+    replayed after an eager route and dispatch of the same T.  Between the
+    capture and the replay the other phase changes its tile regime, so the
+    dispatch would choose the other form of the small tiles (LDS-staged or
+    register-direct) than the captured one.  Experts of several 32-row blocks
+    (up to 201 rows) and more 32-row blocks than a grid of 96-row tiles has
+    workgroups for; y is poisoned before each replay, so a row that no tile
+    computed would show."""
+    import torch
+
+    from tests.test_gpu_layer import _poison_y
+
+    rows = [201, 97, 64, 33, 32, 1, 0, 40]
+    E, E_loc, T = 64, len(rows), sum(rows)
+    spec = LayerSpec("split-capture", E=E, e0=8, E_loc=E_loc, k=1, H=128, I=192, dtype=BF16, T_P=64 * 512, T_D=T)
+    inp = make_layer(spec, seed=51)
+    owner = 8 + np.random.default_rng(52).permutation(np.repeat(np.arange(E_loc), rows))
+    inp.logits[1] = np.where(np.arange(E)[None, :] == owner[:, None], 1.0, -1.0).astype(np.float32)
+    prefill, wide = 64 * 32, 64 * 512  # tokens of the P batches: its prefill tiles, its 256-row tiles
+    g = GpuLayer(inp)
+    try:
+        M = g.M
+        sg = torch.cuda.Stream()
+
+        def dispatch():
+            M.check(M.moe_route(g.ctx, 1, g.logits[1], T, sg))
+            M.check(M.moe_dispatch(g.ctx, 1, g.x[1], sg))
+
+        g.run(0, T=prefill if form == "direct" else wide)
+        torch.cuda.synchronize()
+        dispatch()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=sg):
+            M.check(M.moe_expert_ffn(g.ctx, 1, sg))
+            M.check(M.moe_combine(g.ctx, 1, g.out[1], sg))
+        torch.cuda.synchronize()
+        for rep, p_tokens in enumerate((wide, prefill, wide)):
+            g.run(0, T=p_tokens)
+            torch.cuda.synchronize()
+            dispatch()
+            _poison_y(g, 1)
+            with torch.cuda.stream(sg):
+                graph.replay()
+            torch.cuda.synchronize()
+            assert np.isfinite(g.fetch(1)["y"]).all(), (form, rep)
+            check_phase(g, inp, 1)
+            # the captured calls left the host state at the dispatch
+            M.check(M.moe_phase_reset(g.ctx, 1))
         del graph
     finally:
         g.close()

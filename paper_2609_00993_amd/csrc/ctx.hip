@@ -12,10 +12,10 @@
 // (Section 5.2); a reset is refused until the phase's enqueued work is done
 // (Section 5.3).
 #include <atomic>
-#include <math.h>
 #include <new>
 #include <string.h>
 
+#include "decode_form.h"
 #include "kernels.h"
 #include "moepd.h"
 #include "moepd_turnstile.h"
@@ -473,11 +473,7 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
     // context runs D layers, P's 256-row GEMM2 takes the tile that leaves a CU
     // room for D's decode tiles beside it.
     const bool share = phase == MOE_PHASE_P && c.d_priority_us > 0 && other != -1;
-    // m-tiles of a small batch under even routing: the experts it touches, one
-    // standard deviation above the mean (a few tiles more than one round holds
-    // cost a second one)
-    const double miss = pow(1.0 - (double)c.top_k / c.num_experts, (double)p.T), loc = c.num_local_experts;
-    const double m_tiles_hint = fmin(loc, loc * (1.0 - miss) + sqrt(loc * miss * (1.0 - miss)));
+    const double m_tiles_hint = decode_m_tiles(c.num_experts, c.num_local_experts, c.top_k, p.T);
     // Small tiles of both phases at once: P's leave the CUs LDS for the kernels of
     // a D layer they wait for, and D's fit where one of P's has ended.
     const bool beside = p.regime == 1 && (share || (phase == MOE_PHASE_D && other == 1));

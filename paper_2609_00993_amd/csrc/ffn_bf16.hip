@@ -38,11 +38,10 @@
 //    phase's prefill tiles (which leave 3 KB of LDS) a 32-row tile loads
 //    straight into operand registers instead, with no LDS, so it can share
 //    their CUs.
-#include <math.h>
-
 #include <type_traits>
 
 #include "common.h"
+#include "decode_form.h"
 #include "kernels.h"
 #include "tiles.h"
 #include "pipeline.h"
@@ -317,7 +316,7 @@ __device__ __forceinline__ void gemm_skinny_tile_direct(const GemmArgs& g, const
 // over a layout made when the other would have been chosen.
 constexpr int kDecodeRows = 96;
 constexpr int kDirectRows = 32;
-constexpr int decode_chunks(int per_cu) { return 160 / per_cu / 4 * 256; }  // 16-byte chunks of LDS: whole panels
+constexpr int decode_chunks(int per_cu) { return decode_lds(per_cu, false) / 16; }  // 16-byte chunks of LDS
 constexpr int decode_slots(int mb, int nb, int per_cu) {
   const int n = decode_chunks(per_cu) / ((mb + nb) * 32 * 8);
   return n > 4 ? 4 : n;
@@ -1010,28 +1009,16 @@ hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const vo
       if (gemm == 1) rot ? go(gemm1_swiglu_decode<true, P>) : go(gemm1_swiglu_decode<false, P>);
       else rot ? go(gemm2_down_decode<true, P>) : go(gemm2_down_decode<false, P>);
     };
-    // Workgroups per CU.  Four (three slots of a 32-row tile) while they hold
-    // all the expected tiles, so that few waves keep enough in flight (256 GEMM1
-    // tiles 46 us, 89 with eight), or while their last round is nearly full (skewed
-    // 2048 GEMM1 tiles 391 us, 414 with eight; beside the other phase's tiles,
-    // where few waves fit, D's layer 847 / 909 us).  Else eight with one slot (the
-    // block being multiplied is in registers meanwhile) while these run at once
-    // (1470 GEMM1 tiles 225 us, 252 with four; 0.15 of a round passes unnoticed),
-    // or six if its last round is the fuller (2560 GEMM2 tiles 51 / 58 us).
-    const double tiles = m_tiles_hint * g.n_tiles;
-    auto rounds = [&](int per_cu) { return tiles / (256.0 * per_cu); };
-    auto cost = [&](int per_cu) { return ceil(rounds(per_cu) - 0.15) / rounds(per_cu); };
+    const int rule = decode_form(m_tiles_hint * g.n_tiles);
     // Where both phases run small tiles the caller gives it: six of 24 KB for P,
     // whose tiles wait for D and so must leave D's place kernel some LDS, eight of
     // 20 KB for D, whose tiles then fit where one of P's has ended (700 + 64 tokens
     // at H 7168 with four per CU for D 1384 us a pass, 914 when all tiles took 12
     // KB and found a place beside P's).
     if (!stage) form(std::integral_constant<int, 0>{});
-    else if (per_cu == 6) form(std::integral_constant<int, 6>{});
-    else if (per_cu == 8) form(std::integral_constant<int, 8>{});
-    else if (tiles <= 4 * 256 || cost(4) <= 1.1) form(std::integral_constant<int, 4>{});
-    else if (rounds(8) > 1.15 && cost(6) < cost(8)) form(std::integral_constant<int, 6>{});
-    else form(std::integral_constant<int, 8>{});
+    else if (per_cu == 6 || (per_cu == 0 && rule == kDecodeSix)) form(std::integral_constant<int, kDecodeSix>{});
+    else if (per_cu == 8 || (per_cu == 0 && rule == kDecodeEight)) form(std::integral_constant<int, kDecodeEight>{});
+    else form(std::integral_constant<int, kDecodeFour>{});
   }
   return hipGetLastError();
 }

@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "decode_form.h"
 #include "kernels.h"
 #include "pipeline.h"
 #include "tiles.h"
@@ -709,7 +710,7 @@ __global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) { gemm_mx_
 // 256 skewed ones 225 against 239).  GEMM1's are 32 columns of gate and up,
 // GEMM2's 64 columns.
 constexpr int kMxDecodeRows = 64;
-constexpr int mx_decode_chunks(int per_cu) { return (per_cu == 8 ? 144 : 160) * 64 / per_cu; }
+constexpr int mx_decode_chunks(int per_cu) { return decode_lds(per_cu, true) / 16; }
 constexpr int mx_decode_slots(int mb, int per_cu, bool sc4) {
   const int n = (mx_decode_chunks(per_cu) - (sc4 ? 64 * mx_decode_gathers(mb) : 0)) / mx_decode_slot(mb, sc4);
   return n > 4 ? 4 : n;
@@ -783,17 +784,13 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
       if (gemm == 1) sc4 ? go(gemm_mx_skinny<true, true, P>) : go(gemm_mx_skinny<true, false, P>);
       else sc4 ? go(gemm_mx_skinny<false, true, P>) : go(gemm_mx_skinny<false, false, P>);
     };
-    // Workgroups per CU, as for the bf16 tiles.
-    const double tiles = m_tiles_hint * g.n_tiles;
-    auto rounds = [&](int per_cu) { return tiles / (256.0 * per_cu); };
-    auto cost = [&](int per_cu) { return ceil(rounds(per_cu) - 0.15) / rounds(per_cu); };
+    const int rule = decode_form(m_tiles_hint * g.n_tiles);
     // P's, while D runs layers too: eight, 144 KB, so D's place kernel finds LDS
     // on a CU whose P tiles wait for D (700 + 64 tokens at H 7168 593 us a pass; with
     // eight for D as well 1020).
-    if (beside) form(std::integral_constant<int, 8>{});
-    else if (tiles <= 4 * 256 || cost(4) <= 1.1) form(std::integral_constant<int, 4>{});
-    else if (rounds(8) > 1.15 && cost(6) < cost(8)) form(std::integral_constant<int, 6>{});
-    else form(std::integral_constant<int, 8>{});
+    if (beside || rule == kDecodeEight) form(std::integral_constant<int, kDecodeEight>{});
+    else if (rule == kDecodeSix) form(std::integral_constant<int, kDecodeSix>{});
+    else form(std::integral_constant<int, kDecodeFour>{});
   }
   return hipGetLastError();
 }

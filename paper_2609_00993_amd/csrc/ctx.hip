@@ -15,7 +15,6 @@
 #include <new>
 #include <string.h>
 
-#include "decode_form.h"
 #include "kernels.h"
 #include "moepd.h"
 #include "moepd_turnstile.h"
@@ -220,6 +219,19 @@ int leave(Phase& p, hipStream_t s) {
   }
   p.last_stream = s;
   return MOE_OK;
+}
+
+// Whether the phase's last recorded call is still running: asked from the other
+// phase's calls, possibly on another host thread (the event lives as long as the
+// context).  A query may not break a capture that some thread has open, so it is
+// made in the relaxed mode; "not ready" is an answer and leaves no error behind.
+bool in_flight(const Phase& p) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  const bool busy = hipEventQuery(p.ev) == hipErrorNotReady;
+  if (busy && hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return busy;
 }
 
 // Launch wrapper: brackets the launch with timing events when enabled.
@@ -474,21 +486,26 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
     // room for D's decode tiles beside it.
     const bool share = phase == MOE_PHASE_P && c.d_priority_us > 0 && other != -1;
     const double m_tiles_hint = decode_m_tiles(c.num_experts, c.num_local_experts, c.top_k, p.T);
-    // Small tiles of both phases at once: P's leave the CUs LDS for the kernels of
-    // a D layer they wait for, and D's fit where one of P's has ended.
-    const bool beside = p.regime == 1 && (share || (phase == MOE_PHASE_D && other == 1));
+    // Small tiles of both phases under D-first admission: P's leave the CUs room
+    // for the layers that they wait for, and D's fit in it.  D asks whether P has
+    // work in flight, so a P batch of long ago costs it nothing; a captured D
+    // layer may replay beside any and takes the form that fits.
+    Beside beside = Beside::kNone;
+    if (p.regime == 1 && share) beside = Beside::kLeaveRoom;
+    if (p.regime == 1 && phase == MOE_PHASE_D && c.d_priority_us > 0 && other == 1 &&
+        (p.capturing || in_flight(ctx->ph[MOE_PHASE_P])))
+      beside = Beside::kFit;
     for (int gemm = 1; gemm <= 2; ++gemm) {
       st = timed(p, gemm == 1 ? MOE_KERNEL_GEMM1 : MOE_KERNEL_GEMM2, stream, [&] {
         if (c.dtype == MOE_DTYPE_FP8)
           return launch_ffn_mx(p.regime, gemm, p.b, mx_of(ctx, p),
                                MxWeights{ctx->w.w_gate_up, ctx->w.w_gate_up_scales, ctx->w.w_down, ctx->w.w_down_scales},
-                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, m_tiles_hint,
-                               beside && phase == MOE_PHASE_P,
+                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, m_tiles_hint, beside,
                                yield_of(ctx, phase), stream);
         if (c.dtype == MOE_DTYPE_BF16)
           return launch_ffn_bf16(p.regime, gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden,
                                  c.inter, max_m_tiles, m_tiles_hint, stage, share,
-                                 beside ? (phase == MOE_PHASE_P ? 6 : 8) : 0, yield_of(ctx, phase),
+                                 beside, yield_of(ctx, phase),
                                  ctx->ph[phase ^ 1].b.signal, stream);
         return launch_ffn_f32(gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden, c.inter,
                               max_m_tiles, stream);

@@ -14,16 +14,33 @@ constexpr int kLdsPerCu = 160 * 1024;
 constexpr int kLdsUnit = 1280;
 constexpr int lds_units(int bytes) { return (bytes + kLdsUnit - 1) / kLdsUnit; }
 
-// Workgroups per CU of the staged forms; kDecodeDirect: operands straight into
-// registers, no LDS (bf16 only).
-enum DecodeForm : int { kDecodeDirect = 0, kDecodeFour = 4, kDecodeSix = 6, kDecodeEight = 8 };
+// Workgroups per CU of the staged forms (kDecodeRoom: four, see below);
+// kDecodeDirect: operands straight into registers, no LDS (bf16 only).
+enum DecodeForm : int { kDecodeDirect = 0, kDecodeRoom = 1, kDecodeFour = 4, kDecodeSix = 6, kDecodeEight = 8 };
 
-// LDS bytes of a workgroup.  bf16: whole 4 KB panels of K blocks.  FP8: eight per
-// CU in 144 KB, so that D's place kernel still finds room on a CU whose P tiles
-// wait for D.
+// LDS bytes of a workgroup.
 constexpr int decode_lds(int form, bool mx) {
-  return form == kDecodeFour ? 40960 : form == kDecodeSix ? (mx ? 26880 : 24576) : mx ? 18432 : 20480;
+  return form == kDecodeFour ? 40960
+         : form == kDecodeSix ? (mx ? 26880 : 24576)
+         : form == kDecodeEight ? (mx ? 18432 : 20480)
+                                : 33280;
 }
+
+// Small batches of both phases under D-first admission.  P's tiles wait for a D
+// layer on their CUs, so what they hold must leave D's kernels room, however many of
+// them a CU takes: kDecodeRoom fits four times and leaves 30 KB, a tile of D's
+// form of six.  Without that room D's tiles wait for P's and P's for D, until
+// P's wait budget ends.  Layer pair / D's layer in us, 500 us budget, P + D tokens,
+// synchronised after each pair: P six or eight per CU and D eight (FP8 D by its
+// tiles) -> these forms:
+//   bf16, H 7168, 32 experts    700 + 4  755 / 364 -> 748 / 288   64 + 64  967 / 649 -> 1053 / 670
+//   bf16, H 2560, 64 experts    700 + 64 795 / 693 -> 348 / 169   64 + 64  646 / 544 ->  278 / 179
+//   bf16, H 2048, 32 experts    200 + 64 229 / 124 -> 241 / 136   64 + 64  229 / 129 ->  235 / 133
+//   FP8, H 7168, 32 experts     700 + 64 1167 / 1036 -> 697 / 386
+//   FP8, H 2560, 64 experts     700 + 64 745 / 647 -> 257 / 122
+// P takes this form once the context has run a D layer, since a D layer may start
+// at any time while P's tiles wait; D takes its form while P has work in flight.
+enum class Beside { kNone, kLeaveRoom, kFit };
 
 // m-tiles of a small batch under even routing: the experts it touches, one
 // standard deviation above the mean (a few tiles more than one round holds cost a
@@ -41,7 +58,9 @@ inline double decode_m_tiles(int experts, int local_experts, int top_k, int T) {
 // slot (the block being multiplied is in registers meanwhile) while these run at
 // once (1470 GEMM1 tiles 225 us, 252 with four; 0.15 of a round passes unnoticed),
 // or six if its last round is the fuller (2560 GEMM2 tiles 51 / 58 us).
-inline DecodeForm decode_form(double tiles) {
+inline DecodeForm decode_form(double tiles, Beside beside) {
+  if (beside == Beside::kLeaveRoom) return kDecodeRoom;
+  if (beside == Beside::kFit) return kDecodeSix;
   auto rounds = [&](int per_cu) { return tiles / (256.0 * per_cu); };
   auto cost = [&](int per_cu) { return ceil(rounds(per_cu) - 0.15) / rounds(per_cu); };
   if (tiles <= 4 * 256 || cost(4) <= 1.1) return kDecodeFour;

@@ -41,7 +41,6 @@
 #include <type_traits>
 
 #include "common.h"
-#include "decode_form.h"
 #include "kernels.h"
 #include "tiles.h"
 #include "pipeline.h"
@@ -316,9 +315,9 @@ __device__ __forceinline__ void gemm_skinny_tile_direct(const GemmArgs& g, const
 // over a layout made when the other would have been chosen.
 constexpr int kDecodeRows = 96;
 constexpr int kDirectRows = 32;
-constexpr int decode_chunks(int per_cu) { return decode_lds(per_cu, false) / 16; }  // 16-byte chunks of LDS
-constexpr int decode_slots(int mb, int nb, int per_cu) {
-  const int n = decode_chunks(per_cu) / ((mb + nb) * 32 * 8);
+constexpr int decode_chunks(int form) { return decode_lds(form, false) / 16; }  // 16-byte chunks of LDS
+constexpr int decode_slots(int mb, int nb, int form) {
+  const int n = decode_chunks(form) / ((mb + nb) * 32 * 8);
   return n > 4 ? 4 : n;
 }
 // 32-column blocks of a staged GEMM2 tile: two, which halves the activation
@@ -326,20 +325,20 @@ constexpr int decode_slots(int mb, int nb, int per_cu) {
 // the weight rows start on the same memory channel (ROT; even 128 tokens at H
 // 7168, I 2048: 161 us against 167).
 constexpr int gemm2_blocks(bool rot) { return rot ? 1 : 2; }
-template <bool GATED, bool ROT, int PER_CU>
+template <bool GATED, bool ROT, int FORM>
 __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
   const int L = block_tile(g);
   if (L < 0) return;
   yield_to_window(g.yield);
   TileCoord tc;
-  if constexpr (PER_CU > 0) {
+  if constexpr (FORM != kDecodeDirect) {
     constexpr int NB = GATED ? 2 : gemm2_blocks(ROT);
     tile_at(g, L, kDecodeRows, GATED ? 32 : 32 * NB, tc);
-    __shared__ u32x4 lds[decode_chunks(PER_CU)];
+    __shared__ u32x4 lds[decode_chunks(FORM)];
     const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
-    if (blocks <= 1) gemm_skinny_tile<1, NB, decode_slots(1, NB, PER_CU), GATED, ROT>(g, tc, lds);
-    else if (blocks == 2) gemm_skinny_tile<2, NB, decode_slots(2, NB, PER_CU), GATED, ROT>(g, tc, lds);
-    else gemm_skinny_tile<3, NB, decode_slots(3, NB, PER_CU), GATED, ROT>(g, tc, lds);
+    if (blocks <= 1) gemm_skinny_tile<1, NB, decode_slots(1, NB, FORM), GATED, ROT>(g, tc, lds);
+    else if (blocks == 2) gemm_skinny_tile<2, NB, decode_slots(2, NB, FORM), GATED, ROT>(g, tc, lds);
+    else gemm_skinny_tile<3, NB, decode_slots(3, NB, FORM), GATED, ROT>(g, tc, lds);
   } else {
     tile_at(g, L, kDirectRows, 32 * kDecodeWaves, tc);
     gemm_skinny_tile_direct<GATED, ROT>(g, tc);
@@ -903,13 +902,13 @@ __global__ __launch_bounds__(256) void router_gemm(GemmArgs g) { gemm_ring_dense
 __global__ __launch_bounds__(256) void gemm1_swiglu_wide(GemmArgs g) { gemm_ring_wide<true, 64>(g); }
 __global__ __launch_bounds__(256) void gemm2_down_wide(GemmArgs g) { gemm_ring_wide<false, 64>(g); }
 __global__ __launch_bounds__(256) void gemm2_down_wide_share(GemmArgs g) { gemm_ring_wide<false, 32>(g); }
-template <bool ROT, int PER_CU>
+template <bool ROT, int FORM>
 __global__ __launch_bounds__(64 * kDecodeWaves) void gemm1_swiglu_decode(GemmArgs g) {
-  gemm_skinny<true, ROT, PER_CU>(g);
+  gemm_skinny<true, ROT, FORM>(g);
 }
-template <bool ROT, int PER_CU>
+template <bool ROT, int FORM>
 __global__ __launch_bounds__(64 * kDecodeWaves) void gemm2_down_decode(GemmArgs g) {
-  gemm_skinny<false, ROT, PER_CU>(g);
+  gemm_skinny<false, ROT, FORM>(g);
 }
 
 // ------------------------------------------------------------------ launch
@@ -926,7 +925,7 @@ long long ffn_bf16_handover_words(long long rows_cap, int e_loc, int H) {
 
 hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn,
                            int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool stage, bool share,
-                           int per_cu, YieldTo yield, const int32_t* other_window, hipStream_t s) {
+                           Beside beside, YieldTo yield, const int32_t* other_window, hipStream_t s) {
   GemmArgs g{};
   g.yield = yield;
   g.offsets = b.offsets;
@@ -1004,21 +1003,21 @@ hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const vo
     g.xcd_local = g.n_tiles % 8 == 0 ? 2 : 1;
     const dim3 grid(round8((long long)max_m_tiles * g.n_tiles));
     auto go = [&](auto k) { k<<<grid, 64 * kDecodeWaves, 0, s>>>(g); };
-    auto form = [&](auto per_cu) {
-      constexpr int P = decltype(per_cu)::value;
-      if (gemm == 1) rot ? go(gemm1_swiglu_decode<true, P>) : go(gemm1_swiglu_decode<false, P>);
-      else rot ? go(gemm2_down_decode<true, P>) : go(gemm2_down_decode<false, P>);
+    auto form = [&](auto f) {
+      constexpr int F = decltype(f)::value;
+      if (gemm == 1) rot ? go(gemm1_swiglu_decode<true, F>) : go(gemm1_swiglu_decode<false, F>);
+      else rot ? go(gemm2_down_decode<true, F>) : go(gemm2_down_decode<false, F>);
     };
-    const int rule = decode_form(m_tiles_hint * g.n_tiles);
-    // Where both phases run small tiles the caller gives it: six of 24 KB for P,
-    // whose tiles wait for D and so must leave D's place kernel some LDS, eight of
-    // 20 KB for D, whose tiles then fit where one of P's has ended (700 + 64 tokens
-    // at H 7168 with four per CU for D 1384 us a pass, 914 when all tiles took 12
-    // KB and found a place beside P's).
-    if (!stage) form(std::integral_constant<int, 0>{});
-    else if (per_cu == 6 || (per_cu == 0 && rule == kDecodeSix)) form(std::integral_constant<int, kDecodeSix>{});
-    else if (per_cu == 8 || (per_cu == 0 && rule == kDecodeEight)) form(std::integral_constant<int, kDecodeEight>{});
-    else form(std::integral_constant<int, kDecodeFour>{});
+    if (!stage) {
+      form(std::integral_constant<int, kDecodeDirect>{});
+    } else {
+      switch (decode_form(m_tiles_hint * g.n_tiles, beside)) {
+        case kDecodeRoom: form(std::integral_constant<int, kDecodeRoom>{}); break;
+        case kDecodeSix: form(std::integral_constant<int, kDecodeSix>{}); break;
+        case kDecodeEight: form(std::integral_constant<int, kDecodeEight>{}); break;
+        default: form(std::integral_constant<int, kDecodeFour>{});
+      }
+    }
   }
   return hipGetLastError();
 }

@@ -28,7 +28,6 @@
 #include <type_traits>
 
 #include "common.h"
-#include "decode_form.h"
 #include "kernels.h"
 #include "pipeline.h"
 #include "tiles.h"
@@ -710,28 +709,28 @@ __global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) { gemm_mx_
 // 256 skewed ones 225 against 239).  GEMM1's are 32 columns of gate and up,
 // GEMM2's 64 columns.
 constexpr int kMxDecodeRows = 64;
-constexpr int mx_decode_chunks(int per_cu) { return decode_lds(per_cu, true) / 16; }
-constexpr int mx_decode_slots(int mb, int per_cu, bool sc4) {
-  const int n = (mx_decode_chunks(per_cu) - (sc4 ? 64 * mx_decode_gathers(mb) : 0)) / mx_decode_slot(mb, sc4);
+constexpr int mx_decode_chunks(int form) { return decode_lds(form, true) / 16; }
+constexpr int mx_decode_slots(int mb, int form, bool sc4) {
+  const int n = (mx_decode_chunks(form) - (sc4 ? 64 * mx_decode_gathers(mb) : 0)) / mx_decode_slot(mb, sc4);
   return n > 4 ? 4 : n;
 }
-template <bool GATED, bool SC4, int PER_CU>
+template <bool GATED, bool SC4, int FORM>
 __global__ __launch_bounds__(64 * kMxDecodeWaves) void gemm_mx_skinny(GemmArgsMX g) {
-  __shared__ u32x4 lds[mx_decode_chunks(PER_CU)];
+  __shared__ u32x4 lds[mx_decode_chunks(FORM)];
   const int L = block_tile(g);
   if (L < 0) return;
   yield_to_window(g.yield);
   TileCoord tc;
   tile_at(g, L, kMxDecodeRows, GATED ? 32 : 64, tc);
   const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
-  if (blocks <= 1) gemm_mx_skinny_tile<1, mx_decode_slots(1, PER_CU, SC4), GATED, SC4>(g, tc, lds);
-  else gemm_mx_skinny_tile<2, mx_decode_slots(2, PER_CU, SC4), GATED, SC4>(g, tc, lds);
+  if (blocks <= 1) gemm_mx_skinny_tile<1, mx_decode_slots(1, FORM, SC4), GATED, SC4>(g, tc, lds);
+  else gemm_mx_skinny_tile<2, mx_decode_slots(2, FORM, SC4), GATED, SC4>(g, tc, lds);
 }
 
 static inline int round8_mx(long long v) { return (int)((v + 7) / 8 * 8); }
 
 hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBuffers& mx, const MxWeights& w,
-                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool beside, YieldTo yield,
+                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, Beside beside, YieldTo yield,
                          hipStream_t s) {
   GemmArgsMX g{};
   g.offsets = b.offsets;
@@ -779,18 +778,17 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
     const dim3 grid(round8_mx((long long)max_m_tiles * g.n_tiles));
     const bool sc4 = g.K % 512 == 0 && ((uintptr_t)g.As | (uintptr_t)g.Bs) % 16 == 0;
     auto go = [&](auto k) { k<<<grid, 64 * kMxDecodeWaves, 0, s>>>(g); };
-    auto form = [&](auto per_cu) {
-      constexpr int P = decltype(per_cu)::value;
-      if (gemm == 1) sc4 ? go(gemm_mx_skinny<true, true, P>) : go(gemm_mx_skinny<true, false, P>);
-      else sc4 ? go(gemm_mx_skinny<false, true, P>) : go(gemm_mx_skinny<false, false, P>);
+    auto form = [&](auto f) {
+      constexpr int F = decltype(f)::value;
+      if (gemm == 1) sc4 ? go(gemm_mx_skinny<true, true, F>) : go(gemm_mx_skinny<true, false, F>);
+      else sc4 ? go(gemm_mx_skinny<false, true, F>) : go(gemm_mx_skinny<false, false, F>);
     };
-    const int rule = decode_form(m_tiles_hint * g.n_tiles);
-    // P's, while D runs layers too: eight, 144 KB, so D's place kernel finds LDS
-    // on a CU whose P tiles wait for D (700 + 64 tokens at H 7168 593 us a pass; with
-    // eight for D as well 1020).
-    if (beside || rule == kDecodeEight) form(std::integral_constant<int, kDecodeEight>{});
-    else if (rule == kDecodeSix) form(std::integral_constant<int, kDecodeSix>{});
-    else form(std::integral_constant<int, kDecodeFour>{});
+    switch (decode_form(m_tiles_hint * g.n_tiles, beside)) {
+      case kDecodeRoom: form(std::integral_constant<int, kDecodeRoom>{}); break;
+      case kDecodeSix: form(std::integral_constant<int, kDecodeSix>{}); break;
+      case kDecodeEight: form(std::integral_constant<int, kDecodeEight>{}); break;
+      default: form(std::integral_constant<int, kDecodeFour>{});
+    }
   }
   return hipGetLastError();
 }

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "decode_form.h"
+
 namespace moepd {
 
 // One phase's device buffers (owned by the context, see moepd.h).
@@ -149,8 +151,8 @@ int ffn_bf16_bm(int regime, bool stage);
 // stage (decode regime only): tiles of up to 96 rows, operands as whole lines
 // through a per-wave LDS ring (faster), or 32-row tiles straight into registers
 // with no LDS, which fit on CUs held by the other phase's prefill tiles.
-// m_tiles_hint: expected m-tiles of a small batch under even routing.  per_cu:
-// workgroups per CU of the staged tiles (0: chosen for the expected tiles).  share (256-row
+// m_tiles_hint: expected m-tiles of a small batch under even routing.  beside:
+// what the staged tiles share their CUs with.  share (256-row
 // regime, GEMM2 only): the tiles that leave each CU room for the other
 // phase's staged decode GEMM2 tiles (80 KB of LDS and 364 registers instead
 // of 160 KB and 460; the same bits, 12 % slower alone) run only while the
@@ -160,7 +162,7 @@ int ffn_bf16_bm(int regime, bool stage);
 // does the rest.
 hipError_t launch_ffn_bf16(int regime, int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn,
                            int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool stage, bool share,
-                           int per_cu, YieldTo yield, const int32_t* other_window, hipStream_t s);
+                           Beside beside, YieldTo yield, const int32_t* other_window, hipStream_t s);
 // Words of b.tile_done a phase needs (256-row GEMM2 tiles at its capacity).
 long long ffn_bf16_handover_words(long long rows_cap, int e_loc, int H);
 
@@ -186,8 +188,8 @@ hipError_t launch_permute_mx(const void* x, int T, int k, int H, const int32_t* 
 // expects avg_rows rows per expert, which the place kernel must use.
 int ffn_mx_bm(int regime, long long avg_rows);
 hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBuffers& mx, const MxWeights& w,
-                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, bool beside, YieldTo yield,
-                         hipStream_t s);  // beside: P's small tiles, with D's layers
+                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, Beside beside, YieldTo yield,
+                         hipStream_t s);
 
 int ffn_f32_bm();
 hipError_t launch_ffn_f32(int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn, int e_loc, int H,

@@ -159,3 +159,49 @@ def test_captured_ffn_replays_after_eager_dispatch(form):
         del graph
     finally:
         g.close()
+
+
+def test_eager_d_layer_while_another_thread_captures():
+    """D asks whether P has work in flight, on whatever thread drives it: that
+    must not break a capture that another thread has open in the global mode."""
+    import threading
+
+    import torch
+
+    inp = make_layer(LayerSpec("capture-thread", E=64, e0=0, E_loc=64, k=2, H=256, I=256, dtype=BF16, T_P=300, T_D=20),
+                     seed=53)
+    g = GpuLayer(inp, d_priority_us=200)
+    try:
+        g.run(0)  # a small P batch: D's next layer asks about it
+        g.run(1)
+        torch.cuda.synchronize()
+        ref = _d_state(g)
+        a = torch.ones(1024, device="cuda")
+        b = torch.zeros(1024, device="cuda")
+        torch.cuda.synchronize()
+        failed = []
+
+        def eager():
+            try:
+                torch.cuda.set_device(0)
+                for _ in range(3):
+                    g.run(1)
+            except Exception as e:  # noqa: BLE001 (reported below, on the test's thread)
+                failed.append(e)
+
+        graph, sg = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=sg, capture_error_mode="global"):
+            t = threading.Thread(target=eager)
+            t.start()
+            t.join()
+            torch.add(a, a, out=b)
+        assert not failed, failed
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(b, a + a)
+        got = _d_state(g)
+        for key in ref:
+            assert np.array_equal(got[key], ref[key]), key
+        del graph
+    finally:
+        g.close()

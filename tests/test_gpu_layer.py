@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 import oracle
-from synth import BF16, F32, LayerSpec, make_config, make_layer
+from synth import BF16, F32, FP8, LayerSpec, make_config, make_layer
 from tests.gpu_util import (GpuLayer, assert_close_rms, assert_route_layout_exact, check_h_y, tol_of)
 
 pytestmark = pytest.mark.gpu
@@ -379,6 +379,112 @@ def test_decode_tiles_staged_and_direct_bit_identical(name):
         for key in staged:
             assert np.array_equal(staged[key], direct[key]), key
         check_phase(g, inp, 1)
+    finally:
+        g.close()
+
+
+class _DeviceLayer:
+    """A context over weights, tokens and logits made on the device (no oracle
+    input), for layers of full size."""
+
+    def __init__(self, E, k, H, I, dtype, T, d_priority_us):
+        import torch
+
+        from paper_2609_00993_amd import moepd as M
+
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(53)
+        w, scales = [], [None, None]
+        for n, K in ((2 * I, H), (H, I)):
+            t = torch.randn((E, n, K), generator=gen, device="cuda", dtype=torch.bfloat16)
+            w.append((t * 16).to(torch.float8_e4m3fn).view(torch.uint8) if dtype == FP8 else t.mul_(K ** -0.5))
+        if dtype == FP8:
+            scales = [torch.full((E, n, K // 32), 117, dtype=torch.uint8, device="cuda") for n, K in ((2 * I, H), (H, I))]
+        self.M, self.T = M, T
+        self.logits = [torch.randn((t, E), generator=gen, device="cuda") for t in T]
+        self.x = [torch.randn((t, H), generator=gen, device="cuda").to(torch.bfloat16) for t in T]
+        self.out = [torch.zeros((t, H), device="cuda") for t in T]
+        self.keep = (w, scales)
+        torch.cuda.synchronize()
+        cfg = M.make_config(E, 0, E, k, H, I, M.MOE_DTYPE_FP8 if dtype == FP8 else M.MOE_DTYPE_BF16, *T,
+                            d_priority_us=d_priority_us)
+        st, self.ctx = M.moe_ctx_create(cfg, *w, *scales)
+        M.check(st, "moe_ctx_create")
+        self.streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+
+    def run(self, ph):
+        self.M.layer(self.ctx, ph, self.logits[ph], self.T[ph], self.x[ph], self.out[ph], self.streams[ph])
+
+    def d_layer_us(self, n, beside=False):
+        """Median time of D's layer, alone or enqueued right after a P layer."""
+        import torch
+
+        pairs = []
+        for _ in range(n):
+            torch.cuda.synchronize()
+            if beside:
+                self.run(0)
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record(self.streams[1])
+            self.run(1)
+            b.record(self.streams[1])
+            pairs.append((a, b))
+        torch.cuda.synchronize()
+        return sorted(a.elapsed_time(b) * 1e3 for a, b in pairs)[n // 2]
+
+    def close(self):
+        self.M.check(self.M.moe_ctx_destroy(self.ctx))
+
+
+@pytest.mark.parametrize("dtype,E,k,H,I,T_P,T_D", [
+    (BF16, 64, 1, 2560, 768, 700, 64), (BF16, 64, 1, 2560, 768, 700, 3), (FP8, 64, 1, 2560, 768, 700, 64),
+    (FP8, 32, 1, 7168, 2048, 700, 64),
+])
+def test_small_batches_of_both_phases(dtype, E, k, H, I, T_P, T_D):
+    """Small batches of both phases under D-first admission: P's tiles wait for
+    D's layer in the form that leaves D's tiles room, so D's layer ends long
+    before P's wait budget (1000 us; a D tile that finds no room waits for P's to
+    give up), and each phase gives the bits it gives alone."""
+    import torch
+
+    solo = []
+    for ph in (0, 1):
+        g = _DeviceLayer(E, k, H, I, dtype, (T_P, T_D), 1000)
+        try:
+            g.run(ph)
+            torch.cuda.synchronize()
+            solo.append(g.out[ph].clone())
+        finally:
+            g.close()
+    g = _DeviceLayer(E, k, H, I, dtype, (T_P, T_D), 1000)
+    try:
+        for ph in (1, 0, 1):
+            g.run(ph)
+        alone, beside = g.d_layer_us(9), g.d_layer_us(9, beside=True)
+        print(f"[both small] D's layer {alone:.0f} us alone, {beside:.0f} us beside P", flush=True)
+        for ph in (0, 1):
+            assert torch.equal(g.out[ph], solo[ph]), ph
+        assert beside < alone + 600, (alone, beside)
+    finally:
+        g.close()
+
+
+def test_small_p_batch_of_long_ago_costs_d_nothing():
+    """D's tiles take the form that fits beside P's small tiles only while P has
+    work in flight: a P batch that has ended long ago leaves D's layer as fast
+    as before the context's first P layer (with the form for it kept, a D batch
+    of a few tokens took a third longer)."""
+    import torch
+
+    g = _DeviceLayer(16, 2, 7168, 2048, BF16, (100, 2), 500)
+    try:
+        g.run(1)
+        before = min(g.d_layer_us(9) for _ in range(3))
+        g.run(0)
+        torch.cuda.synchronize()
+        after = min(g.d_layer_us(9) for _ in range(3))
+        print(f"[history] D's layer {before:.1f} us, after a small P batch {after:.1f} us", flush=True)
+        assert after < 1.15 * before, (before, after)
     finally:
         g.close()
 

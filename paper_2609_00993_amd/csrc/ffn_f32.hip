@@ -18,6 +18,7 @@
 // I 1024 64 tokens 451 + 247 -> 130 + 73, 2048 tokens 1077 + 637 -> 937 + 570.
 #include "common.h"
 #include "kernels.h"
+#include "tiles.h"
 
 namespace moepd {
 
@@ -44,7 +45,8 @@ __device__ __forceinline__ bool tile_lookup_f(const GemmArgsF& g, int bm, int bn
   __syncthreads();
   const int total = s_tb[g.e_loc] * g.n_tiles;
   const int per_xcd = (total + 7) >> 3;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int block = blockIdx.x + blockIdx.y * gridDim.x;
+  const int xcd = block & 7, slot = block >> 3;
   if (slot >= per_xcd) return false;
   const int L = xcd * per_xcd + slot;
   if (L >= total) return false;
@@ -170,9 +172,9 @@ hipError_t launch_ffn_f32(int gemm, const PhaseBuffers& b, const void* w_gu, con
   g.n_tiles = g.N / 32;
   const long long blocks = ((long long)max_m_tiles * g.n_tiles + 7) / 8 * 8;
   if (gemm == 1)
-    gemm_f32<true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
+    gemm_f32<true><<<grid_of(blocks, 256), dim3(256), 0, s>>>(g);
   else
-    gemm_f32<false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(g);
+    gemm_f32<false><<<grid_of(blocks, 256), dim3(256), 0, s>>>(g);
   return hipGetLastError();
 }
 

@@ -147,6 +147,15 @@ __device__ __forceinline__ int block_tile(const G& g) {
   return tile_of_block<DENSE>(g, (int)blockIdx.x);
 }
 
+// Grid of `blocks` workgroups of `threads`: a dimension holds fewer than 2^32
+// work-items (past that it silently wraps), so larger launches take rows of x
+// workgroups, a multiple of 8 (workgroup x + gridDim.x y then stays on XCD x % 8), and
+// the last row may hold surplus ids.
+inline dim3 grid_of(long long blocks, int threads) {
+  const long long most = ((1LL << 32) / threads - 1) / 8 * 8;
+  return blocks <= most ? dim3((unsigned)blocks) : dim3((unsigned)most, (unsigned)((blocks + most - 1) / most));
+}
+
 // D first (Section 3.1): the planner admits ready D work before P, and a
 // long P execution is cut into segments so that D advances between them
 // (Section 4.2).  On one GPU a segment is a run of K slices of a GEMM tile:

@@ -130,6 +130,14 @@ int main() {
       launches += 5;
     }
   }
+  // grids: every id, dimensions of fewer than 2^32 work-items, whole rows of XCDs
+  const long long most_blocks = ((16LL << 20) / 32 + kMaxLocalExperts) * (16384 / 32);  // the float32 GEMMs' largest
+  for (long long blocks : {8LL, 256LL, 1LL << 23, (1LL << 24) - 8, 1LL << 24, (1LL << 24) + 8, 1LL << 25, most_blocks}) {
+    const dim3 g = grid_of(blocks, 256);
+    const long long ids = (long long)g.x * g.y;
+    CHECK((long long)g.x * 256 < 1LL << 32 && g.x % 8 == 0 && ids >= blocks && ids - blocks < g.x && ids < 1LL << 31,
+          "grid of %lld blocks: %u x %u", blocks, g.x, g.y);
+  }
   if (failures) {
     std::printf("%d failures\n", failures);
     return 1;

@@ -181,6 +181,42 @@ def test_f32_tiles(H, I):
         g.close()
 
 
+def test_f32_layer_of_more_workgroups_than_one_grid_dimension():
+    """A grid dimension holds fewer than 2^32 work-items: 16 million of the
+    float32 GEMM's workgroups.  2^20 tokens on two experts of 8256 columns need
+    more (h takes 69 GB).  Sampled tokens against float64."""
+    import torch
+
+    from paper_2609_00993_amd import moepd as M
+
+    E, k, H, I, T = 2, 2, 64, 8256, 1 << 20
+    if torch.cuda.mem_get_info()[0] < 90 << 30:
+        pytest.skip("needs 90 GB of device memory")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(54)
+    w = [torch.randn((E, n, K), generator=gen, device="cuda") * K ** -0.5 for n, K in ((2 * I, H), (H, I))]
+    x = torch.randn((T, H), generator=gen, device="cuda")
+    logits = torch.randn((T, E), generator=gen, device="cuda")
+    out = torch.full((T, H), float("nan"), device="cuda")
+    torch.cuda.synchronize()
+    st, ctx = M.moe_ctx_create(M.make_config(E, 0, E, k, H, I, M.MOE_DTYPE_F32, T, 0), *w)
+    M.check(st, "moe_ctx_create")
+    try:
+        M.layer(ctx, 0, logits, T, x, out, torch.cuda.Stream())
+        torch.cuda.synchronize()
+        assert torch.isfinite(out).all()
+        t = torch.cat([torch.arange(0, T, 4099, device="cuda"), torch.tensor([T - 1], device="cuda")])
+        gate = torch.softmax(logits[t].double(), dim=1)
+        ref = torch.zeros((t.numel(), H), dtype=torch.float64, device="cuda")
+        for e in range(E):
+            a = x[t].double() @ w[0][e].double().t()
+            ref += gate[:, e:e + 1] * ((torch.nn.functional.silu(a[:, :I]) * a[:, I:]) @ w[1][e].double().t())
+        err = (out[t].double() - ref).abs().max() / ref.square().mean().sqrt()
+        assert err < 1e-5, float(err)
+    finally:
+        M.check(M.moe_ctx_destroy(ctx))
+
+
 def _snapshot(g, ph):
     res = g.fetch(ph)
     return {k: v.copy() for k, v in res.items() if isinstance(v, np.ndarray)}

@@ -166,7 +166,9 @@ typedef struct moe_config {
  * FP8 contexts pass E4M3 codes there and the E8M0 scale bytes in
  *   w_gate_up_scales [E_loc, 2I, H / 32], w_down_scales [E_loc, H, I / 32]
  * (scale b of a row covers its values [32 b, 32 b + 32)); other contexts
- * pass NULL.  They must stay valid for the context's lifetime. */
+ * pass NULL.  They must stay valid for the context's lifetime.  No pointer needs
+ * more than its element's alignment (16-byte alignment of the scales lets FP8
+ * layers read them in fewer pieces). */
 typedef struct moe_weights {
   const void* w_gate_up;
   const void* w_down;

@@ -292,7 +292,12 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream);
  * tokens with no resident slot get a zero row.  The receive side of DeepEP's
  * combine (Section 2.2) on this GPU's share of the experts: summing the
  * shares of all expert-parallel ranks gives the layer's output.
- * out: borrowed device [T, H] float32; every row is written.
+ * out: borrowed [T, H] float32 on the context's device; every row is written.
+ * Work enqueued on that device after this call sees it by stream order.  For
+ * the host (out in mapped host memory) or another device to see it, the caller
+ * synchronises as HIP asks: a stream, a device or an event of its own.
+ * moe_phase_reset and moe_ctx_destroy tell that the work has ended and publish
+ * nothing.
  * Errors: MOE_ERR_INVALID_ARG (null out with T > 0), MOE_ERR_INVALID_PHASE,
  * MOE_ERR_STATE, MOE_ERR_HIP. */
 int moe_combine(moe_ctx_t* ctx, int phase, void* out, hipStream_t stream);

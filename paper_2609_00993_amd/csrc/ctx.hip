@@ -175,7 +175,8 @@ int alloc_phase(moe_ctx* ctx, int phase) {
   if (hipMemset(base + o_cnt, 0, o_ros - o_cnt) != hipSuccess) return MOE_ERR_HIP;
   if (hipMemset(base + o_tb, 0, off - o_tb) != hipSuccess) return MOE_ERR_HIP;
   // The phase event orders streams of this device and answers "is the work
-  // done"; nothing on the host is published through it, so it carries no
+  // done"; nothing is published to the host or another device through it (the
+  // header leaves that to the caller's own synchronisation), so it carries no
   // system-scope fence.  With the fence each of a layer's four records held
   // the stream for about 3 us, without it for about 1.5 us (a 64-token mid-size
   // decode layer 102.8 -> 96.6 us, 91.0 with no records at all).

@@ -5,8 +5,9 @@
 // rows [offsets[e], offsets[e+1]) without overlap, none longer than the tile
 // height and none empty, for every n-tile.  Shapes: the 256-row tiles dealt
 // to the XCDs in groups (GEMM1 in super-rows of one grid round, GEMM2 in the
-// plain order), the prefill tiles (160 and 192 rows) with the rows shared evenly, and the
-// 32-row decode tiles (striped over the XCDs or in contiguous ranges), over
+// plain order), the prefill tiles (bf16 160 rows, FP8 192 and 256) with the rows
+// shared evenly, and the decode tiles (bf16 96 rows staged and 32 register-direct,
+// FP8 64; striped over the XCDs or in contiguous ranges), over
 // random and skewed row counts and the edges (empty experts, one row, exact
 // multiples of the tile height).
 //
@@ -28,7 +29,7 @@ struct G {
   int dense_rows, dense_splits, dense_ks, dense_total;
 };
 
-static int failures = 0;
+static int failures = 0, launches = 0;
 #define CHECK(cond, ...)                   \
   do {                                     \
     if (!(cond)) {                         \
@@ -45,6 +46,7 @@ static int failures = 0;
 // and the grid the launcher would use.
 static void check_launch(const std::vector<int>& rows, int bm, int n_tiles, int n_group, int m_super, int xcd_local,
                          const char* what) {
+  ++launches;
   const int e_loc = (int)rows.size();
   std::vector<int32_t> off(e_loc + 1, 0), tb(e_loc + 1, 0);
   long long R = 0;
@@ -113,7 +115,6 @@ int main() {
   cases.push_back({1});
   cases.push_back({4097, 0, 0, 2303, 2398});
   cases.push_back({0, 0, 0});
-  int launches = 0;
   for (const auto& rows : cases) {
     for (int n_tiles : {1, 2, 3, 16, 28, 32, 64}) {
       // 256-row tiles, grouped over the XCDs: GEMM1 with super-rows of one
@@ -122,12 +123,12 @@ int main() {
       check_launch(rows, 256, n_tiles, 4, ms, 3, "wide super-rows");
       check_launch(rows, 256, n_tiles, 4, 0, 3, "wide plain");
       check_launch(rows, 256, n_tiles, 8, 5, 3, "wide odd super-rows");
-      // 160- and 192-row tiles, consecutive tiles on one XCD, rows shared evenly
+      // prefill tiles, consecutive tiles on one XCD, rows shared evenly
       check_launch(rows, 160, n_tiles, 1, 0, 1, "prefill");
-      check_launch(rows, 192, n_tiles, 1, 0, 1, "prefill");
-      // 32-row decode tiles: striped when the n-tiles are a multiple of 8
-      check_launch(rows, 32, n_tiles, 1, 0, n_tiles % 8 == 0 ? 2 : 1, "decode");
-      launches += 5;
+      check_launch(rows, 192, n_tiles, 1, 0, 1, "prefill FP8");
+      check_launch(rows, 256, n_tiles, 1, 0, 1, "prefill FP8 tall");
+      // decode tiles: striped when the n-tiles are a multiple of 8
+      for (int bm : {96, 64, 32}) check_launch(rows, bm, n_tiles, 1, 0, n_tiles % 8 == 0 ? 2 : 1, "decode");
     }
   }
   // grids: every id, dimensions of fewer than 2^32 work-items, whole rows of XCDs

@@ -9,6 +9,8 @@ import subprocess
 
 import pytest
 
+from synth import BF16, FP8
+from tests import test_gpu_decode_forms as forms
 from tests.kernel_resources import VGPRS_PER_LANE, kernels
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -48,3 +50,32 @@ def test_a_d_tile_fits_beside_waiting_p_tiles():
         p = max(got[n.format(ROOM)][0] for n in names)
         d = max(got[n.format(SIX)][0] for n in names)
         assert p + d <= VGPRS_PER_LANE, (p, d)
+
+
+def _form(check, E, e_loc, k, T, n_tiles):
+    r = subprocess.run([check, "form"] + [str(v) for v in (E, e_loc, k, T, n_tiles)], stdout=subprocess.PIPE, text=True,
+                       timeout=60)
+    return int(r.stdout)
+
+
+def _n_tiles(dtype, H, I):
+    """Column tiles of a launch of staged tiles: GEMM1's are 32 columns of gate
+    and up, GEMM2's 64 columns, 32 for bf16 with a rotated K."""
+    rot = dtype == BF16 and I % 2048 == 0
+    return I // 32, H // (32 if rot else 64)
+
+
+def test_gpu_shapes_take_the_forms_they_name(check):
+    """The edge rows of the GPU test run in every form that a launch by its tile
+    count can take: each type, GEMM, and K order or scale gather, four, six and
+    eight workgroups per CU; the FP8 ones are compared with four."""
+    seen = set()
+    for dtype, H, I, form1, form2 in forms.SHAPES:
+        n1, n2 = _n_tiles(dtype, H, I)
+        got = [_form(check, forms.E, forms.E_LOC, 1, forms.T, n) for n in (n1, n2)]
+        assert got == [form1, form2], (dtype, H, I, got)
+        special = (H % 2048 == 0, I % 2048 == 0) if dtype == BF16 else (H % 512 == 0, I % 512 == 0)
+        seen |= {(dtype, gemm, special[gemm], got[gemm]) for gemm in (0, 1)}
+        if dtype == FP8:
+            assert [_form(check, forms.E_FOUR, forms.E_LOC, 1, forms.T, n) for n in (n1, n2)] == [4, 4], (H, I)
+    assert seen == {(d, gemm, s, f) for d in (BF16, FP8) for gemm in (0, 1) for s in (False, True) for f in (4, 6, 8)}

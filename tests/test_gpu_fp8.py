@@ -196,8 +196,8 @@ def test_fp8_ring_heights(rows, H, I):
 
 # The small-batch tiles: 32-row blocks and one to three tiles of 64 rows at their
 # edges; K blocks with and without the four-block scale gathers, fewer and more
-# than the ring's slots; tile counts that choose four, eight (16 experts x 80
-# or 128 column tiles) and six (16 x 160) workgroups per CU.
+# than the ring's slots; tile counts of GEMM1 that choose four, eight (16 experts
+# x 80 column tiles) and six (16 x 160) workgroups per CU.
 @pytest.mark.parametrize("H,I", [(128, 128), (384, 256), (512, 640), (128, 2560), (512, 4096), (128, 5120)])
 def test_fp8_decode_heights(H, I):
     rows = [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 0, 2, 3, 40, 5]

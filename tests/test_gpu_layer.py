@@ -140,8 +140,8 @@ def test_prefill_tile_heights(H, I):
 
 # The staged decode tiles: 32-row blocks and one to three tiles of 96 rows at
 # their edges, K blocks fewer and more than the ring's slots, rotated K (rows of
-# a multiple of 4 KB) or not, and tile counts that choose four, eight (16 experts
-# x 80 or 128 column tiles) and six (16 x 160) workgroups per CU.
+# a multiple of 4 KB) or not, and tile counts of GEMM1 that choose four, eight (16
+# experts x 80 column tiles) and six (16 x 160) workgroups per CU.
 @pytest.mark.parametrize("H,I", [(64, 64), (192, 320), (128, 2560), (2048, 128), (4096, 64), (64, 4096), (128, 5120)])
 def test_decode_tile_heights(H, I):
     rows = [1, 31, 32, 33, 64, 65, 95, 96, 97, 128, 192, 193, 0, 2, 3, 40]

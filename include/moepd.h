@@ -153,8 +153,8 @@ typedef struct moe_config {
    * at least 512 rows per expert expected) never wait, since each holds a
    * whole CU; once the context has run a D layer, a GEMM2 tile that starts
    * while a D layer is in flight takes a form that leaves its CU room for
-   * D's tiles instead.  P's tiles of small batches, which wait on their CUs,
-   * leave them that room from then on.  A scheduling hint only: results are
+   * D's tiles instead.  P's tiles of small batches wait from then on, and
+   * leave their CUs that room.  A scheduling hint only: results are
    * unchanged. */
   int32_t d_priority_us;
 } moe_config_t;

@@ -493,6 +493,9 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
     // layer may replay beside any and takes the form that fits.
     Beside beside = Beside::kNone;
     if (p.regime == 1 && share) beside = Beside::kLeaveRoom;
+    // Before the context's first D layer P's small tiles take the CUs whole, so
+    // they do not wait for it either.
+    const YieldTo yield = p.regime == 1 && other == -1 ? YieldTo{nullptr, 0, 0} : yield_of(ctx, phase);
     if (p.regime == 1 && phase == MOE_PHASE_D && c.d_priority_us > 0 && other == 1 &&
         (p.capturing || in_flight(ctx->ph[MOE_PHASE_P])))
       beside = Beside::kFit;
@@ -501,13 +504,11 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
         if (c.dtype == MOE_DTYPE_FP8)
           return launch_ffn_mx(p.regime, gemm, p.b, mx_of(ctx, p),
                                MxWeights{ctx->w.w_gate_up, ctx->w.w_gate_up_scales, ctx->w.w_down, ctx->w.w_down_scales},
-                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, m_tiles_hint, beside,
-                               yield_of(ctx, phase), stream);
+                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, m_tiles_hint, beside, yield, stream);
         if (c.dtype == MOE_DTYPE_BF16)
           return launch_ffn_bf16(p.regime, gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden,
                                  c.inter, max_m_tiles, m_tiles_hint, stage, share,
-                                 beside, yield_of(ctx, phase),
-                                 ctx->ph[phase ^ 1].b.signal, stream);
+                                 beside, yield, ctx->ph[phase ^ 1].b.signal, stream);
         return launch_ffn_f32(gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden, c.inter,
                               max_m_tiles, stream);
       });

@@ -38,8 +38,8 @@ constexpr int decode_lds(int form, bool mx) {
 //   bf16, H 2048, 32 experts    200 + 64 229 / 124 -> 241 / 136   64 + 64  229 / 129 ->  235 / 133
 //   FP8, H 7168, 32 experts     700 + 64 1167 / 1036 -> 697 / 386
 //   FP8, H 2560, 64 experts     700 + 64 745 / 647 -> 257 / 122
-// P takes this form once the context has run a D layer, since a D layer may start
-// at any time while P's tiles wait; D takes its form while P has work in flight.
+// P takes this form, and waits, once the context has run a D layer, since a D layer
+// may start at any time; D takes its form while P has work in flight.
 enum class Beside { kNone, kLeaveRoom, kFit };
 
 // m-tiles of a small batch under even routing: the experts it touches, one

@@ -494,13 +494,13 @@ def test_small_batches_of_both_phases(dtype, E, k, H, I, T_P, T_D):
             g.close()
     g = _DeviceLayer(E, k, H, I, dtype, (T_P, T_D), 1000)
     try:
-        for ph in (1, 0, 1):
-            g.run(ph)
+        # the context's first layers of either phase, then its later ones
+        first = g.d_layer_us(1, beside=True)
         alone, beside = g.d_layer_us(9), g.d_layer_us(9, beside=True)
-        print(f"[both small] D's layer {alone:.0f} us alone, {beside:.0f} us beside P", flush=True)
+        print(f"[both small] D's layer {alone:.0f} us alone, {beside:.0f} us beside P, first {first:.0f}", flush=True)
         for ph in (0, 1):
             assert torch.equal(g.out[ph], solo[ph]), ph
-        assert beside < alone + 600, (alone, beside)
+        assert max(first, beside) < alone + 600, (alone, beside, first)
     finally:
         g.close()
 

@@ -259,7 +259,7 @@ WindowSignal window_of(moe_ctx* ctx, int phase) {
 // The P phase's grouped GEMMs hold back while the D window is open; one poll
 // sleeps 127 * 64 cycles, about 3.4 us at 2.4 GHz.  Not for tiles whose
 // workgroups hold too many registers for a D GEMM wave to share their SIMDs
-// (the bf16 256-row tiles, 460 VGPRs; the MX FP8 ring tiles, 512): a P
+// (the bf16 256-row tiles, 464 and 392 VGPRs; the MX FP8 ring tiles, 512): a P
 // workgroup waiting on its CU would only keep D off it.
 YieldTo yield_of(moe_ctx* ctx, int phase) {
   if (phase != MOE_PHASE_P || ctx->cfg.d_priority_us <= 0) return YieldTo{nullptr, 0, 0};
@@ -484,7 +484,7 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
     const int max_m_tiles = (int)((rows + bm - 1) / bm) + c.num_local_experts;
     // D first (Section 3.1) on one GPU: while D-first admission is on and the
     // context runs D layers, P's 256-row GEMM2 takes the tile that leaves a CU
-    // room for D's decode tiles beside it.
+    // room for D's small kernels beside it.
     const bool share = phase == MOE_PHASE_P && c.d_priority_us > 0 && other != -1;
     const double m_tiles_hint = decode_m_tiles(c.num_experts, c.num_local_experts, c.top_k, p.T);
     // Small tiles of both phases under D-first admission: P's leave the CUs room

@@ -233,7 +233,7 @@ __device__ __forceinline__ void gemm_skinny_tile(const GemmArgs& g, const TileCo
   }
 }
 
-// The same tile with each operand loaded straight into MFMA lane layout (16
+// The same for 32 rows, with each operand loaded straight into MFMA lane layout (16
 // bytes from each of 32 rows per instruction) and no LDS: slower alone, but
 // it fits on a CU beside a prefill tile of the other phase, whose
 // ring leaves 3 KB of LDS free.
@@ -348,7 +348,7 @@ __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
 // One workgroup of 4 waves computes a BM x BN output tile of one expert.
 // Per BK-deep K slice it stages A (BM rows) and B (BR weight rows: BN gate +
 // BN up rows when GATED, BN rows otherwise) in LDS, swizzled as above.  The
-// slices travel HBM -> LDS by global_load_lds_dwordx4 (lane l of an
+// slices travel HBM -> LDS by buffer_load_dwordx4 ... lds (lane l of an
 // instruction lands 16 bytes at base + 16 l, so the swizzle is applied on the
 // global side) into a ring of STAGES slots; no register or ds_write is spent
 // on staging.
@@ -359,7 +359,7 @@ __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
 //    STAGES - 1 slices are in flight while one is multiplied.  The group goes
 //    out in parts over the next slice's substeps (see PART_N).  Only this
 //    wave's DMA instructions (and older stores) count in vmcnt, and loads
-//    complete in order, so wait_vmcnt(n * per-slice count) retires exactly
+//    complete in order, so a wait down to the newer slices' count retires exactly
 //    the slices needed: every group is issued whole before the next begins;
 //  * fragments: each 16-deep substep's A/B fragments are read from LDS into
 //    one of two register sets while the MFMAs of the previous substep run on
@@ -371,8 +371,10 @@ __device__ __forceinline__ void gemm_skinny(const GemmArgs& g) {
 // Wave (wm, wn) of the WM x WN wave grid owns rows [wm WTM, +WTM) and output
 // columns [wn WTN, +WTN) (for GATED, the gate and the up column of the same
 // index, so the SwiGLU is applied in registers).  The K loop is branch-free:
-// rows past the expert's end are clamped to its last row and discarded at
-// the store, which keeps the MFMA and LDS-read schedule intact.
+// rows past the expert's end lie outside the buffer resource (they come as zeros,
+// with no memory request) and are not stored, which keeps the MFMA and LDS-read
+// schedule intact.
+//
 // Slices between the in-tile checks of the D window (a power of two).
 constexpr int kPauseEvery = 4;
 
@@ -893,12 +895,17 @@ __global__ __launch_bounds__(256) void router_gemm(GemmArgs g) { gemm_ring_dense
 // and three activation slots, the activations one slice ahead and their DMA
 // spread over the next slice's substeps, in 64-deep slices (160 KB; at the
 // 16384-token skewed batch 4 % faster than 32-deep slices in four stages for
-// GEMM1, 8 % for GEMM2).  GEMM2's share form takes 32-deep slices (80 KB,
-// 364 registers), which leaves a CU room for D's staged GEMM2 tiles beside
-// it: at that batch D's layer under P took 985 us against 1360-1400 us
-// beside the 64-deep form (460 registers) and 1085 us beside a four-stage
-// ring of 32-deep slices (128 KB).  Nothing of D's GEMM1 fits beside GEMM1's
-// tile in either depth (456-460 registers).
+// GEMM1, 8 % for GEMM2).  GEMM2's share form takes 32-deep slices (80 KB and
+// 352 registers, where the 64-deep form takes all the LDS and 392), which leaves
+// a CU room for D's layout kernels and, where these are one block of 32 columns
+// (K a multiple of 2048, at most 160 registers), D's staged GEMM2 tiles: at that
+// batch D's layer of 256 tokens under P takes 850 us, 1040 with the 64-deep form
+// alone.  Tiles of two blocks (200 registers and more) do not fit beside it, and D
+// gains from it all the same (256-row batches at H 2048, I 1024: D of 64 tokens 212
+// us against 240, at H 2560, I 768 221 against 237); one block there, which would
+// fit, made D's layer 1 to 3 % longer.  P's passes beside a D that never stops take
+// 7 to 22 % longer for it.  Nothing of D's GEMM1 fits beside GEMM1's tile (464
+// registers).
 __global__ __launch_bounds__(256) void gemm1_swiglu_wide(GemmArgs g) { gemm_ring_wide<true, 64>(g); }
 __global__ __launch_bounds__(256) void gemm2_down_wide(GemmArgs g) { gemm_ring_wide<false, 64>(g); }
 __global__ __launch_bounds__(256) void gemm2_down_wide_share(GemmArgs g) { gemm_ring_wide<false, 32>(g); }

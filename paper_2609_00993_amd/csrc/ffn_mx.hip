@@ -698,6 +698,9 @@ __device__ __forceinline__ void gemm_mx_ring(const GemmArgsMX& g) {
   else MOEPD_MX_RING(256, 2, 2, 2, 2, SC4);
 #undef MOEPD_MX_RING
 }
+// Seven bodies share each kernel's registers; with the four-slice scale gathers
+// these are all 512, and five (GEMM1) and four (GEMM2) values are spilled around
+// the K loops, none inside them.
 template <bool SC4>
 __global__ __launch_bounds__(256) void gemm1_mx_prefill(GemmArgsMX g) { gemm_mx_ring<true, SC4>(g); }
 template <bool SC4>

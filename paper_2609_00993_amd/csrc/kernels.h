@@ -144,7 +144,7 @@ hipError_t launch_combine(const void* y, const float* topk_w, const int32_t* row
 
 // Grouped expert FFN.  `regime` picks the tile configuration (0 = large
 // batches, tiles of up to 160 rows; 1 = small batches, weight-streaming tiles of
-// one wave; 2 = very large batches, 256-row tiles);
+// one wave and up to 96 rows; 2 = very large batches, 256-row tiles);
 // ffn_bf16_bm gives its m-tile height, which the place kernel must use for
 // tile_base (small batches: the staged form's; with stage false 32, tile_base32).
 int ffn_bf16_bm(int regime, bool stage);
@@ -154,8 +154,8 @@ int ffn_bf16_bm(int regime, bool stage);
 // m_tiles_hint: expected m-tiles of a small batch under even routing.  beside:
 // what the staged tiles share their CUs with.  share (256-row
 // regime, GEMM2 only): the tiles that leave each CU room for the other
-// phase's staged decode GEMM2 tiles (80 KB of LDS and 364 registers instead
-// of 160 KB and 460; the same bits, 12 % slower alone) run only while the
+// phase's small kernels (80 KB of LDS and 352 registers instead of 160 KB and
+// 392; the same bits, 11 to 19 % slower alone) run only while the
 // other phase has a layer in flight: a first launch of the full tiles does
 // every tile that starts while `other_window` (the other phase's signal word)
 // is 0 and marks it in b.tile_done, and a second launch of the share form

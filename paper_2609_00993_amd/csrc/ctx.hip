@@ -66,7 +66,7 @@ struct moe_ctx {
   int device;
   int esz;
   Phase ph[MOE_NUM_PHASES];
-  // Tile regime of each phase's latest bf16 expert-FFN launch (-1: none).
+  // Tile regime of each phase's latest expert-FFN launch (-1: none).
   // The other phase reads it (possibly from another host thread) to choose
   // its decode tiles: prefill tiles leave 3 KB of a CU's LDS free,
   // too little for the LDS-staged decode tile, so beside them the phase takes

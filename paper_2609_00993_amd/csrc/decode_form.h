@@ -18,7 +18,8 @@ constexpr int lds_units(int bytes) { return (bytes + kLdsUnit - 1) / kLdsUnit; }
 // kDecodeDirect: operands straight into registers, no LDS (bf16 only).
 enum DecodeForm : int { kDecodeDirect = 0, kDecodeRoom = 1, kDecodeFour = 4, kDecodeSix = 6, kDecodeEight = 8 };
 
-// LDS bytes of a workgroup.
+// LDS bytes of a workgroup.  Eight: what one slot of the tallest tile takes (bf16 96
+// rows, FP8 64 rows and their scales).
 constexpr int decode_lds(int form, bool mx) {
   return form == kDecodeFour ? 40960
          : form == kDecodeSix ? (mx ? 26880 : 24576)

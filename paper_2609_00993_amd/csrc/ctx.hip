@@ -259,7 +259,7 @@ WindowSignal window_of(moe_ctx* ctx, int phase) {
 // The P phase's grouped GEMMs hold back while the D window is open; one poll
 // sleeps 127 * 64 cycles, about 3.4 us at 2.4 GHz.  Not for tiles whose
 // workgroups hold too many registers for a D GEMM wave to share their SIMDs
-// (the bf16 256-row tiles, 464 and 392 VGPRs; the MX FP8 ring tiles, 512): a P
+// (the bf16 256-row tiles, 464 and 392 VGPRs; the MX FP8 ring tiles, 408 to 512): a P
 // workgroup waiting on its CU would only keep D off it.
 YieldTo yield_of(moe_ctx* ctx, int phase) {
   if (phase != MOE_PHASE_P || ctx->cfg.d_priority_us <= 0) return YieldTo{nullptr, 0, 0};
@@ -504,7 +504,8 @@ int moe_expert_ffn(moe_ctx_t* ctx, int phase, hipStream_t stream) {
         if (c.dtype == MOE_DTYPE_FP8)
           return launch_ffn_mx(p.regime, gemm, p.b, mx_of(ctx, p),
                                MxWeights{ctx->w.w_gate_up, ctx->w.w_gate_up_scales, ctx->w.w_down, ctx->w.w_down_scales},
-                               c.num_local_experts, c.hidden, c.inter, max_m_tiles, m_tiles_hint, beside, yield, stream);
+                               c.num_local_experts, c.hidden, c.inter, p.bm, max_m_tiles, m_tiles_hint, beside,
+                               yield, stream);
         if (c.dtype == MOE_DTYPE_BF16)
           return launch_ffn_bf16(p.regime, gemm, p.b, ctx->w.w_gate_up, ctx->w.w_down, c.num_local_experts, c.hidden,
                                  c.inter, max_m_tiles, m_tiles_hint, stage, share,

@@ -371,13 +371,16 @@ __device__ __forceinline__ void gemm_mx_skinny_tile(const GemmArgsMX& g, const T
 // (with a group's gathers in flight, two instructions more).
 constexpr int mx_scale_rows(int bm) { return (bm + 63) / 64 * 64; }  // A rows in whole gathers
 constexpr int kMxB = 256;                                             // weight rows of a ring tile
-constexpr int kMxMaxRows = 256;                                       // rows of the tallest ring tile
+constexpr int kMxTallRows = 256;                                      // rows of the tallest ring tile
+constexpr int kMxRingRows = 192;                                      // and of the others
 // 16-byte chunks of LDS: the rings, and the scale area in its larger form.
 constexpr int mx_ring_chunks(int bm, int sa, int sb) {
   return sa * bm * 8 + sb * kMxB * 8 + (sa > 4 ? sa : 4) * (mx_scale_rows(bm) + kMxB) / 4;
 }
 
-template <int BM, int WM, int WN, int SA, int SB, bool GATED, bool SC4>
+// TALL names the kernel that the body is part of (gemm_mx_ring): each has its own,
+// since the host pass cannot use one body from two kernels.
+template <int BM, int WM, int WN, int SA, int SB, bool GATED, bool SC4, bool TALL>
 __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const TileCoord& tc, u32x4* lds) {
   constexpr int BR = kMxB;
   constexpr int NB = GATED ? 2 : 1;
@@ -674,37 +677,43 @@ __device__ __forceinline__ void gemm_mx_ring_body(const GemmArgsMX& g, const Til
 //   256                  444 / 236 -> 317 / 204
 //   512                  616 / 365 -> 521 / 353
 // and with 47 rows per expert at H 2560, I 768 (64 experts) 90 / 50 -> 65 / 43.
-constexpr int kMxRingChunks = 160 * 1024 / 16;
-template <bool GATED, bool SC4>
+//
+// TALL: the batch's m-tiles hold up to 256 rows (ffn_mx_bm), else up to 192.
+// Without the 256-row body a kernel takes 440 registers and 151 KB of LDS instead of
+// 512 and 160, spills nothing, and leaves a CU room for the other phase's route,
+// permute and combine waves: at 512 experts, H 2560, I 768, D's layer of 256 tokens
+// under 8192-token prefills 199 -> 169 us, with the prefill alone as fast.
+constexpr int mx_lds_chunks(bool tall) { return tall ? 160 * 1024 / 16 : mx_ring_chunks(kMxRingRows, 2, 3); }
+template <bool GATED, bool SC4, bool TALL>
 __device__ __forceinline__ void gemm_mx_ring(const GemmArgsMX& g) {
-  __shared__ u32x4 lds[kMxRingChunks];
+  __shared__ u32x4 lds[mx_lds_chunks(TALL)];
   const int L = block_tile(g);
   if (L < 0) return;
   yield_to_window(g.yield);
   TileCoord tc;
-  tile_at(g, L, kMxMaxRows, GATED ? 128 : 256, tc);
+  tile_at(g, L, TALL ? kMxTallRows : kMxRingRows, GATED ? 128 : 256, tc);
   const int blocks = __builtin_amdgcn_readfirstlane((tc.m_end - tc.m0 + 31) / 32);
 #define MOEPD_MX_RING(BM, WM, WN, SA, SB, SC4)                                           \
   do {                                                                                   \
-    static_assert(mx_ring_chunks(BM, SA, SB) <= kMxRingChunks, "ring exceeds the LDS"); \
-    gemm_mx_ring_body<BM, WM, WN, SA, SB, GATED, SC4>(g, tc, lds);                       \
+    static_assert(mx_ring_chunks(BM, SA, SB) <= mx_lds_chunks(TALL), "ring exceeds the LDS"); \
+    gemm_mx_ring_body<BM, WM, WN, SA, SB, GATED, SC4, TALL>(g, tc, lds);                     \
   } while (0)
   if (blocks <= 1) MOEPD_MX_RING(32, 1, 4, 3, 4, SC4);
   else if (blocks == 2) MOEPD_MX_RING(64, 1, 4, 3, 3, SC4);
   else if (blocks == 3) MOEPD_MX_RING(96, 1, 4, 3, 3, SC4);
   else if (blocks == 4) MOEPD_MX_RING(128, 1, 4, 3, 3, SC4);
   else if (blocks == 5) MOEPD_MX_RING(160, 1, 4, 2, 3, SC4);
-  else if (blocks == 6) MOEPD_MX_RING(192, 2, 2, 2, 3, SC4);
-  else MOEPD_MX_RING(256, 2, 2, 2, 2, SC4);
+  else if (!TALL || blocks == 6) MOEPD_MX_RING(192, 2, 2, 2, 3, SC4);
+  else if constexpr (TALL) MOEPD_MX_RING(256, 2, 2, 2, 2, SC4);
 #undef MOEPD_MX_RING
 }
-// Seven bodies share each kernel's registers; with the four-slice scale gathers
-// these are all 512, and five (GEMM1) and four (GEMM2) values are spilled around
-// the K loops, none inside them.
-template <bool SC4>
-__global__ __launch_bounds__(256) void gemm1_mx_prefill(GemmArgsMX g) { gemm_mx_ring<true, SC4>(g); }
-template <bool SC4>
-__global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) { gemm_mx_ring<false, SC4>(g); }
+// With the 256-row body and the four-slice scale gathers the registers are all
+// 512, and five (GEMM1) and four (GEMM2) values are spilled around the K loops, none
+// inside them.
+template <bool SC4, bool TALL>
+__global__ __launch_bounds__(256) void gemm1_mx_prefill(GemmArgsMX g) { gemm_mx_ring<true, SC4, TALL>(g); }
+template <bool SC4, bool TALL>
+__global__ __launch_bounds__(256) void gemm2_mx_prefill(GemmArgsMX g) { gemm_mx_ring<false, SC4, TALL>(g); }
 
 // Small-batch tiles of up to kMxDecodeRows rows, cut to their 32-row blocks (64 is
 // what one slot and the scales of the eight-per-CU form take; with 96 rows and
@@ -733,8 +742,8 @@ __global__ __launch_bounds__(64 * kMxDecodeWaves) void gemm_mx_skinny(GemmArgsMX
 static inline int round8_mx(long long v) { return (int)((v + 7) / 8 * 8); }
 
 hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBuffers& mx, const MxWeights& w,
-                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, Beside beside, YieldTo yield,
-                         hipStream_t s) {
+                         int e_loc, int H, int I, int bm, int max_m_tiles, double m_tiles_hint, Beside beside,
+                         YieldTo yield, hipStream_t s) {
   GemmArgsMX g{};
   g.offsets = b.offsets;
   g.tile_base = b.tile_base;
@@ -773,8 +782,13 @@ hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBu
     // a row's scales of four slices in one aligned 16-byte gather
     const bool sc4 = g.K % 512 == 0 && ((uintptr_t)g.As | (uintptr_t)g.Bs) % 16 == 0;
     auto go = [&](auto k) { k<<<grid, 256, 0, s>>>(g); };
-    if (gemm == 1) sc4 ? go(gemm1_mx_prefill<true>) : go(gemm1_mx_prefill<false>);
-    else sc4 ? go(gemm2_mx_prefill<true>) : go(gemm2_mx_prefill<false>);
+    if (bm == kMxTallRows) {
+      if (gemm == 1) sc4 ? go(gemm1_mx_prefill<true, true>) : go(gemm1_mx_prefill<false, true>);
+      else sc4 ? go(gemm2_mx_prefill<true, true>) : go(gemm2_mx_prefill<false, true>);
+    } else {
+      if (gemm == 1) sc4 ? go(gemm1_mx_prefill<true, false>) : go(gemm1_mx_prefill<false, false>);
+      else sc4 ? go(gemm2_mx_prefill<true, false>) : go(gemm2_mx_prefill<false, false>);
+    }
   } else {
     g.n_tiles = g.N / (gemm == 1 ? 32 : 64);
     g.xcd_local = g.n_tiles % 8 == 0 ? 2 : 1;
@@ -810,7 +824,7 @@ int ffn_mx_bm(int regime, long long avg_rows) {
   long long dev = 0;
   while ((dev + 1) * (dev + 1) <= avg_rows) ++dev;
   const long long r = avg_rows + dev;
-  return (r + kMxMaxRows - 1) / kMxMaxRows < (r + 191) / 192 ? kMxMaxRows : 192;
+  return (r + kMxTallRows - 1) / kMxTallRows < (r + kMxRingRows - 1) / kMxRingRows ? kMxTallRows : kMxRingRows;
 }
 
 }  // namespace moepd

@@ -188,8 +188,8 @@ hipError_t launch_permute_mx(const void* x, int T, int k, int H, const int32_t* 
 // expects avg_rows rows per expert, which the place kernel must use.
 int ffn_mx_bm(int regime, long long avg_rows);
 hipError_t launch_ffn_mx(int regime, int gemm, const PhaseBuffers& b, const MxBuffers& mx, const MxWeights& w,
-                         int e_loc, int H, int I, int max_m_tiles, double m_tiles_hint, Beside beside, YieldTo yield,
-                         hipStream_t s);
+                         int e_loc, int H, int I, int bm, int max_m_tiles, double m_tiles_hint, Beside beside,
+                         YieldTo yield, hipStream_t s);
 
 int ffn_f32_bm();
 hipError_t launch_ffn_f32(int gemm, const PhaseBuffers& b, const void* w_gu, const void* w_dn, int e_loc, int H,

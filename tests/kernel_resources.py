@@ -13,6 +13,11 @@ READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", 
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 VGPRS_PER_LANE = 512  # of a SIMD, shared by its waves
 VGPR_UNIT = 8
+LDS_UNITS = 128  # of a CU, 1280 bytes each
+
+
+def lds_units(nbytes):
+    return -(-nbytes // 1280)
 
 
 def _code_objects():

@@ -11,7 +11,7 @@ import pytest
 
 from synth import BF16, FP8
 from tests import test_gpu_decode_forms as forms
-from tests.kernel_resources import VGPRS_PER_LANE, kernels
+from tests.kernel_resources import LDS_UNITS, VGPRS_PER_LANE, kernels, lds_units
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2609_00993_amd", "csrc")
@@ -50,6 +50,19 @@ def test_a_d_tile_fits_beside_waiting_p_tiles():
         p = max(got[n.format(ROOM)][0] for n in names)
         d = max(got[n.format(SIX)][0] for n in names)
         assert p + d <= VGPRS_PER_LANE, (p, d)
+
+
+def test_d_small_kernels_fit_beside_fp8_ring_tiles():
+    """P's FP8 ring tiles of up to 192 rows leave a SIMD the registers of D's route,
+    permute and combine waves, and a CU some LDS (the taller ones take it all)."""
+    got = kernels()
+    small = max(v[0] for k, v in got.items()
+                if k.startswith(("route_kernel", "permute_mx_kernel", "combine_kernel<2, 2")))
+    for gemm in (1, 2):
+        for sc4 in ("false", "true"):
+            vgprs, lds = got[f"gemm{gemm}_mx_prefill<{sc4}, false>"]
+            assert vgprs + small <= VGPRS_PER_LANE, (gemm, sc4, vgprs, small)
+            assert lds_units(lds) < LDS_UNITS, (gemm, sc4, lds)
 
 
 def _form(check, E, e_loc, k, T, n_tiles):
